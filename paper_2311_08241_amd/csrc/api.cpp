@@ -228,8 +228,6 @@ se_status make_plan(const std::vector<const HostMesh *> &members, const std::vec
     p->nE_host = ht.nE;
     static_assert(sizeof(TileHdr) == sizeof(TileHdrK), "tile header layouts differ");
     SE_TRY(p->hdr.upload(ht.hdr.data(), ht.hdr.size() * sizeof(TileHdr)));
-    SE_TRY(p->nV.upload(ht.nV.data(), ht.nV.size() * 4));
-    SE_TRY(p->nE.upload(ht.nE.data(), ht.nE.size() * 4));
     SE_TRY(p->lv_gid.upload(ht.lv_gid.data(), ht.lv_gid.size() * 4));
     const int64_t nle = static_cast<int64_t>(ht.le_gid.size());
     {
@@ -813,8 +811,6 @@ static TileArgs tile_args(const se_mesh *m, const DevTiles &P, bool f32, const s
     TileArgs a{};
     a.nt = stream_policy(m->h.nv, f32);
     a.hdr = P.hdr.as<const TileHdrK>();
-    a.nV = P.nV.as<const int32_t>();
-    a.nE = P.nE.as<const int32_t>();
     a.lv_gid = P.lv_gid.as<const int32_t>();
     a.le_rec = P.le_rec.as<const uint32_t>();
     a.cs_row = P.cs_row.as<const uint16_t>();
@@ -1486,9 +1482,7 @@ se_status se_subcycle_adjoint(se_mesh *m, const se_params *p, const void *eta0, 
         auto traj_of = [&](int32_t sg) { return static_cast<void *>(w + A.etraj + (sg & 1) * traj_bytes); };
         AdjTileArgs ra{};
         ra.hdr = P.hdr.as<const TileHdrK>();
-        ra.nV = P.nV.as<const int32_t>();
-        ra.nE = P.nE.as<const int32_t>();
-        ra.lv_gid = P.lv_gid.as<const int32_t>();
+            ra.lv_gid = P.lv_gid.as<const int32_t>();
         ra.le_rec = P.le_rec.as<const uint32_t>();
         ra.cs_row = P.cs_row.as<const uint16_t>();
         ra.lgeo = f32 ? P.geo32.p : P.geo64.p;
@@ -1954,8 +1948,6 @@ se_status se_subcycle_batched(se_batch *b, const se_params *p, se_state *st, con
     TileArgs a{};
     a.nt = stream_policy(b->nv, f32);
     a.hdr = P.hdr.as<const TileHdrK>();
-    a.nV = P.nV.as<const int32_t>();
-    a.nE = P.nE.as<const int32_t>();
     a.lv_gid = P.lv_gid.as<const int32_t>();
     a.le_rec = P.le_rec.as<const uint32_t>();
     a.cs_row = P.cs_row.as<const uint16_t>();

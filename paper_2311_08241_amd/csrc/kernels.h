@@ -33,11 +33,13 @@ __host__ __device__ constexpr int own_slots(int ept) { return ept <= 2 ? ept : e
 
 struct TileHdrK {   // mirror of TileHdr (same layout)
     int32_t vbase, nv0, ebase, nown, lv_off, le_off, cs_off, rw_off, member, mtile, p0, p1;
+    int32_t nV[9], nE[9];   // cumulative level counts
+    int32_t p2, p3;
 };
 
 struct TileArgs {
     const TileHdrK *hdr;
-    const int32_t *nV, *nE, *lv_gid;
+    const int32_t *lv_gid;
     const uint32_t *le_rec;     // per local triangle, 4 words: global id, packed local
                                 // vertices and flux positions (3 words)
     const uint16_t *cs_row;
@@ -86,7 +88,7 @@ struct TileArgs {
 // s_hi - cnt, on a tile and cnt rings of halo (the forward tile kernel's rings).
 struct AdjTileArgs {
     const TileHdrK *hdr;
-    const int32_t *nV, *nE, *lv_gid;
+    const int32_t *lv_gid;
     const uint32_t *le_rec;
     const uint16_t *cs_row;
     const void *lgeo, *lae;     // per local triangle: gbx gby gcx gcy; A_e

@@ -586,6 +586,14 @@ __global__ void __launch_bounds__(256) k_sesm_fin(PlainArgs a) {
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int align16(int b) { return (b + 15) & ~15; }
 
+// Workgroup barrier ordering LDS accesses only: unlike __syncthreads it does not wait
+// for the wave's global stores (the recompute's trajectory) or loads in flight.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // SM: the AB3-AM4 (SESM) substep instead of the forward-backward one.  The state a
 // launch hands to the next is (eta, eta^{-1}, eta^{-2}, eta_am) at vertices and
 // (U, U^{-1}, U_ab) at triangles, with the transport update of the last substep
@@ -647,8 +655,8 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
     const bool track = (c.flags & KF_TRACK_VOLUME) != 0;
     const bool linear_h = (c.flags & KF_LINEAR_H) != 0;
     const bool hasW = a.W != nullptr;
-    const int *nV = a.nV + b * (K + 1);   // level counts of the tile (uniform loads)
-    const int *nE = a.nE + b * (K + 1);
+    const int *nV = a.hdr[b].nV;   // level counts of the tile (uniform loads)
+    const int *nE = a.hdr[b].nE;
     const int nv_load = nV[rings], ne_load = nE[rings], nvu = nV[rings - 1 - (VI ? 1 : 0)];
     const int tid = threadIdx.x;
 
@@ -974,7 +982,21 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
             if (i < h.nv0) v0 += rAv64[k] * (double)sEta[i];
         }
         for (int i = tid + VO * BLOCK; i < h.nv0; i += BLOCK) v0 += a.Av64[h.vbase + i] * (double)sEta[i];
+        v0 = wave_sum_last(v0);
+        if ((tid & 63) == 63) red[8 * NW + (tid >> 6)] = v0;
     }
+    // FP32 forward-backward: the wave's volume partial of a substep is summed while the
+    // next substep's elevation reads are in flight (vdef, its red slot jdef), the last one
+    // before its barrier; the other forms, which hold more registers, sum it at once
+    // (deferring cost AB3-AM4 1% and FP64 0.4% on the lat-lon mesh).
+    constexpr bool DEFER = F32 && FB;
+    double vdef = 0.0;
+    int jdef = -1;
+    auto vol_flush = [&]() {   // by DPP: no LDS round trips
+        vdef = wave_sum_last(vdef);
+        if ((tid & 63) == 63) red[jdef * NW + (tid >> 6)] = vdef;
+        jdef = -1;
+    };
     bool dry_any = false, bad_any = false;
     const T gd = cg<T>(c) * dts, th = cth<T>(c);
     const float eref = F32 ? c.eta_ref_f : 0.0f;
@@ -1016,6 +1038,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
                 hE[3 * r + 2] = sEta[t1[r] & 0xffffu];
             }
         }
+        if (DEFER && jdef >= 0) vol_flush();
         if constexpr (VI) {
             const int ne_u = sLev[9 + lev + 1];
 #pragma unroll
@@ -1029,7 +1052,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
                     sUb[2 * le + 1] = rUy[r] / He;
                 }
             }
-            __syncthreads();
+            lds_barrier();
         }
 #pragma unroll
         for (int r = 0; r < EPT; ++r) {
@@ -1149,7 +1172,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
                 }
             }
         }
-        __syncthreads();
+        lds_barrier();
         // vertex phase.  The update of vertex i from its row sum acc (and its elevation,
         // area term and W read beforehand)
         auto finish = [&](int i, T acc, T e_i, T av_i, T w_i) -> T {
@@ -1248,11 +1271,12 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
             if (vol_j && i < h.nv0) vp += a.Av64[h.vbase + i] * (double)en;
             if (TR && trj && i < h.nv0) trj[i] = en;
         }
-        if (vol_j) {   // by DPP: no LDS round trips before the barrier
-            vp = wave_sum_last(vp);
-            if ((tid & 63) == 63) red[j * NW + (tid >> 6)] = vp;
+        if (vol_j) {
+            vdef = vp;
+            jdef = j;
+            if (!DEFER || j + 1 == cnt) vol_flush();
         }
-        __syncthreads();
+        lds_barrier();
     }
     if (dry_any) set_fault(a.faults, 1u);
     if (bad_any) set_fault(a.faults, 2u);
@@ -1314,27 +1338,17 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
         }
     }
     }
-    // volume partials of this tile
-    if (first) {
-        v0 = wave_sum_last(v0);
-        if ((tid & 63) == 63) red[8 * NW + (tid >> 6)] = v0;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        double *vp = a.vol_part + c.vol_off;
-        if (first) {
-            double s = 0.0;
-            for (int w = 0; w < NW; ++w) s += red[8 * NW + w];
-            vp[h.mtile] = s;
-        }
-        for (int j = 0; j < cnt; ++j) {
-            const bool keep = track || (last && j == cnt - 1);
-            if (!keep) continue;
-            double s = 0.0;
-            for (int w = 0; w < NW; ++w) s += red[j * NW + w];
-            const int64_t row = track ? (m0 + j + 1) : 1;
-            vp[row * c.ntiles + h.mtile] = s;
-        }
+    // volume partials of this tile, lane j the waves' sums of substep j in wave order
+    // (the last substep's barrier made them visible), lane 8 those of the initial state:
+    // one thread adding all of them in a chain of LDS reads ended each launch about 0.5 us
+    // later (with the counts in the header and the LDS-only barriers, 61,897 vertices FP64
+    // 190 -> 181 us per 47-substep call, 524,288 vertices FP32 596 -> 579 us per 60)
+    if (tid <= 8 && (tid == 8 ? first : tid < cnt && (track || (last && tid == cnt - 1)))) {
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) s += red[tid * NW + w];
+        const int64_t row = tid == 8 ? 0 : track ? (m0 + tid + 1) : 1;
+        (a.vol_part + c.vol_off)[row * c.ntiles + h.mtile] = s;
     }
 }
 
@@ -1550,8 +1564,8 @@ __device__ __forceinline__ void adj_tile_body(const AdjTileArgs &a, int b, int G
     constexpr bool nt = false;
     const StepC c = a.c;
     const int K = a.K, cnt = a.cnt;
-    const int *nV = a.nV + b * (K + 1);
-    const int *nE = a.nE + b * (K + 1);
+    const int *nV = a.hdr[b].nV;
+    const int *nE = a.hdr[b].nE;
     const int nv_load = nV[cnt], ne_load = nE[cnt], nvu = nV[cnt - 1];
     const int tid = threadIdx.x;
     const bool nonlin = !(c.flags & KF_LINEAR_H);
@@ -1772,7 +1786,7 @@ __device__ __forceinline__ void adj_tile_body(const AdjTileArgs &a, int b, int G
             lUx[r] = lUox;
             lUy[r] = lUoy;
         }
-        __syncthreads();
+        lds_barrier();
         // vertex phase: lambda_eta += sum over the vertex's triangles (ascending) of
         // the slot term and lambda_H / 3; the H0 gradient of owned vertices
         auto vsum = [&](int i, T &ghv, bool own) {
@@ -1806,7 +1820,7 @@ __device__ __forceinline__ void adj_tile_body(const AdjTileArgs &a, int b, int G
             T dummy = T(0);
             vsum(i, dummy, false);
         }
-        __syncthreads();
+        lds_barrier();
     }
 
     // write back the owned entries (the last launch: with the final step's work)

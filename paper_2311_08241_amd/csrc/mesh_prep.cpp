@@ -516,6 +516,10 @@ se_status build_tile_range(const HostMesh &m, size_t mi, int64_t voff, int64_t e
         out.cs_row.push_back(static_cast<uint16_t>(nent));
         while (out.cs_row.size() % 4) out.cs_row.push_back(0);   // 8-byte vector loads
         out.n_ent += nent;
+        for (int32_t i = 0; i <= K; ++i) {
+            h.nV[i] = nVl[i];
+            h.nE[i] = nEl[i];
+        }
         out.hdr.push_back(h);
         for (int32_t i = 0; i <= K; ++i) {
             out.nV.push_back(nVl[i]);

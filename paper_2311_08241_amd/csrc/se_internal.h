@@ -70,6 +70,10 @@ struct TileHdr {
     int32_t member;         // batch member (0 for a single mesh)
     int32_t mtile;          // tile index within its member
     int32_t pad0, pad1;
+    // cumulative level counts |V_i|, |E_i|, i = 0..K (K <= 8; entry 0: owned), in the
+    // header so that one scalar load brings everything a tile starts from
+    int32_t nV[9], nE[9];
+    int32_t pad2, pad3;
 };
 
 struct HostTiles {
@@ -126,7 +130,7 @@ struct DevTiles {
     }
     bool ok(bool f32, bool sm) const { return sm ? (f32 ? ok_sm32 : ok_sm64) : (f32 ? ok32 : ok64); }
     std::vector<TileHdr> hdr_host;
-    DevBuf hdr, nV, nE, lv_gid, le_rec, cs_row;
+    DevBuf hdr, lv_gid, le_rec, cs_row;
     DevBuf geo64, geo32, ae64, ae32;   // per local triangle: 4 gradient values; A_e
     DevBuf lav64, lav32;          // per local vertex: 1 / A_v (FP64, FP32)
     // host copies for tables built on first use: global id of each local triangle,

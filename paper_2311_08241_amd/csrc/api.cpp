@@ -184,7 +184,8 @@ se_status plan_host(const std::vector<const HostMesh *> &members, const std::vec
     for (int f = 0; f < 2; ++f) {
         const double s = f == 0 ? 4.0 : 8.0;
         const double bytes = sumV * (4 + 2 * s) + sumVu * (s + 2) + sumC * 0.0 +
-                             sumE * (4 + 12 + 5 * s + 2 * s + 2 * s + s) +
+                             sumE * (ht.ell ? 8 : 12) + (sumE - ne) * 4 +
+                             sumE * (5 * s + 2 * s + 2 * s + s) +
                              ne * (32.0 + 2 * s) + nv * (s + 8.0);
         (f == 0 ? st.bytes_per_vs_f32 : st.bytes_per_vs_f64) = bytes / (static_cast<double>(nv) * K);
     }
@@ -230,13 +231,17 @@ se_status make_plan(const std::vector<const HostMesh *> &members, const std::vec
     SE_TRY(p->hdr.upload(ht.hdr.data(), ht.hdr.size() * sizeof(TileHdr)));
     SE_TRY(p->lv_gid.upload(ht.lv_gid.data(), ht.lv_gid.size() * 4));
     const int64_t nle = static_cast<int64_t>(ht.le_gid.size());
-    {
-        std::vector<uint32_t> rec(4 * nle);
+    SE_TRY(p->le_gid.upload(ht.le_gid.data(), ht.le_gid.size() * 4));
+    if (ht.ell) {
+        SE_TRY(p->le_rec.upload(ht.le_rank.data(), ht.le_rank.size() * 4));
+    } else {
+        std::vector<uint32_t> rec(2 * nle), pos(nle);
         for (int64_t i = 0; i < nle; ++i) {
-            rec[4 * i] = static_cast<uint32_t>(ht.le_gid[i]);
-            for (int k = 0; k < 3; ++k) rec[4 * i + 1 + k] = ht.le_tri[3 * i + k];
+            for (int k = 0; k < 2; ++k) rec[2 * i + k] = ht.le_tri[3 * i + k];
+            pos[i] = ht.le_tri[3 * i + 2];
         }
         SE_TRY(p->le_rec.upload(rec.data(), rec.size() * 4));
+        SE_TRY(p->le_pos.upload(pos.data(), pos.size() * 4));
     }
     SE_TRY(p->cs_row.upload(ht.cs_row.data(), ht.cs_row.size() * 2));
     // local geometry per tile, gathered member by member
@@ -813,6 +818,8 @@ static TileArgs tile_args(const se_mesh *m, const DevTiles &P, bool f32, const s
     a.hdr = P.hdr.as<const TileHdrK>();
     a.lv_gid = P.lv_gid.as<const int32_t>();
     a.le_rec = P.le_rec.as<const uint32_t>();
+    a.le_pos = P.le_pos.as<const uint32_t>();
+    a.le_gid = P.le_gid.as<const int32_t>();
     a.cs_row = P.cs_row.as<const uint16_t>();
     a.lgeo = f32 ? P.geo32.p : P.geo64.p;
     a.lae = f32 ? P.ae32.p : P.ae64.p;
@@ -1484,6 +1491,8 @@ se_status se_subcycle_adjoint(se_mesh *m, const se_params *p, const void *eta0, 
         ra.hdr = P.hdr.as<const TileHdrK>();
             ra.lv_gid = P.lv_gid.as<const int32_t>();
         ra.le_rec = P.le_rec.as<const uint32_t>();
+        ra.le_pos = P.le_pos.as<const uint32_t>();
+        ra.le_gid = P.le_gid.as<const int32_t>();
         ra.cs_row = P.cs_row.as<const uint16_t>();
         ra.lgeo = f32 ? P.geo32.p : P.geo64.p;
         ra.lae = f32 ? P.ae32.p : P.ae64.p;
@@ -1950,6 +1959,8 @@ se_status se_subcycle_batched(se_batch *b, const se_params *p, se_state *st, con
     a.hdr = P.hdr.as<const TileHdrK>();
     a.lv_gid = P.lv_gid.as<const int32_t>();
     a.le_rec = P.le_rec.as<const uint32_t>();
+    a.le_pos = P.le_pos.as<const uint32_t>();
+    a.le_gid = P.le_gid.as<const int32_t>();
     a.cs_row = P.cs_row.as<const uint16_t>();
     a.lgeo = f32 ? P.geo32.p : P.geo64.p;
     a.lae = f32 ? P.ae32.p : P.ae64.p;

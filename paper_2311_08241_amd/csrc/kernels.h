@@ -40,8 +40,11 @@ struct TileHdrK {   // mirror of TileHdr (same layout)
 struct TileArgs {
     const TileHdrK *hdr;
     const int32_t *lv_gid;
-    const uint32_t *le_rec;     // per local triangle, 4 words: global id, packed local
-                                // vertices and flux positions (3 words)
+    // per local triangle: 2 words (ell: local vertices and row ranks; otherwise the
+    // packed local vertices and one flux position, the other two in le_pos) and the
+    // global id (read for halo triangles only)
+    const uint32_t *le_rec, *le_pos;
+    const int32_t *le_gid;
     const uint16_t *cs_row;
     const void *lgeo;           // per local triangle: gbx, gby, gcx, gcy (4 values)
     const void *lae;            // per local triangle: A_e
@@ -89,7 +92,8 @@ struct TileArgs {
 struct AdjTileArgs {
     const TileHdrK *hdr;
     const int32_t *lv_gid;
-    const uint32_t *le_rec;
+    const uint32_t *le_rec, *le_pos;
+    const int32_t *le_gid;
     const uint16_t *cs_row;
     const void *lgeo, *lae;     // per local triangle: gbx gby gcx gcy; A_e
     const void *Av, *H0, *f;    // global numbering, the precision's type

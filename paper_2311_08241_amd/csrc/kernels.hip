@@ -594,6 +594,30 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Records of a tile's local triangles, 8 bytes each.  Fixed-width rows: f01 = fa | fb << 16
+// and fc, f = local vertex << 3 | rank of the triangle in the vertex's row, from which the
+// packed local vertices and flux positions follow (position
+// 7 vertex + rank = f - vertex).  Compact rows: t0 and t1 themselves, t2 from le_pos.  The
+// global id of an owned triangle or vertex follows from the tile's range; the id tables
+// are read for the halo only (the lanes of owned entries all read the first halo entry, so
+// that no branch separates the loads of a round).  Bound by memory latency and bytes;
+// 8 instead of 16 bytes per triangle, ids of the halo alone and all of a round's loads in
+// flight at once (FP64 staged its vertices slot by slot before): 2.2M vertices FP64 4.52 ->
+// 4.25 ms per 80-substep call, FP32 2.45 -> 2.42, AB3-AM4 FP32 at 550k 1.46 -> 1.41 ms,
+// 61,897 vertices FP64 181 -> 174 us, an ensemble of 24 basins 675 -> 651 us.
+// Deposits for vertices the launch never updates (v >= nvu, beyond the rows) go to the 64
+// scratch slots past the rows: a position is at most top = kEllWidth nvu + lane.
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void tri_unpack(uint32_t &t0, uint32_t &t1, uint32_t &t2, uint32_t top) {
+    static_assert(kEllWidth == 7, "position of a rank: 7 vertex + rank = f - vertex");
+    const uint32_t f01 = t0, f2 = t1;
+    const u16x2 tt = {static_cast<uint16_t>(top), static_cast<uint16_t>(top)};
+    t0 = (f01 >> 3) & 0x1fff1fffu;
+    t2 = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(
+             __builtin_bit_cast(u16x2, f01 - t0), tt));
+    t1 = (f2 >> 3) | (min(f2 - (f2 >> 3), top) << 16);
+}
+
 // SM: the AB3-AM4 (SESM) substep instead of the forward-backward one.  The state a
 // launch hands to the next is (eta, eta^{-1}, eta^{-2}, eta_am) at vertices and
 // (U, U^{-1}, U_ab) at triangles, with the transport update of the last substep
@@ -711,14 +735,15 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
     const T *Wt = static_cast<const T *>(a.W);
     const T *lav = static_cast<const T *>(a.lv_av) + h.lv_off;   // 1 / A_v
     const int32_t *lv = a.lv_gid + h.lv_off;
-    // vertex slots per thread staged in the rounds (the rest, for large tiles on
-    // small workgroups, in a loop afterwards)
-    constexpr int VS = F32 ? (BLOCK >= 512 ? 3072 / BLOCK : 8) : 2;
+    // vertex slots per thread staged in the rounds: a tile has about half as many
+    // vertices as triangles (the rest, if any, in a loop afterwards)
+    constexpr int VS = EPT / 2 + 1;
     int gv[VS];
 #pragma unroll
-    for (int u = 0; u < VS; ++u) gv[u] = lv[min(tid + u * BLOCK, nv_load - 1)];
+    for (int u = 0; u < VS; ++u) gv[u] = lv[min(max(tid + u * BLOCK, h.nv0), nv_load - 1)];
 
-    const uint4 *lrec = reinterpret_cast<const uint4 *>(a.le_rec) + h.le_off;
+    const uint2 *lrec = reinterpret_cast<const uint2 *>(a.le_rec) + h.le_off;
+    const int32_t *lgid = a.le_gid + h.le_off;
     const T *lgeo = static_cast<const T *>(a.lgeo) + 4 * (int64_t)h.le_off;
     const T *lae = static_cast<const T *>(a.lae) + h.le_off;
     const T2 *Uin = static_cast<const T2 *>(
@@ -751,11 +776,11 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
 #pragma unroll
         for (int r = 0; r < EPT; ++r) {
             const int lc = min(tid + r * BLOCK, ne_load - 1);
-            const uint4 rec = ldp<nt>(lrec + lc);
-            gt[r] = (int)rec.x;
-            t0[r] = rec.y;
-            t1[r] = rec.z;
-            t2[r] = rec.w;
+            const uint2 rec = ldp<nt>(lrec + lc);
+            t0[r] = rec.x;
+            t1[r] = rec.y;
+            gt[r] = lgid[min(max(lc, h.nown), ne_load - 1)];
+            if (!a.ell) t2[r] = a.le_pos[h.le_off + lc];
             if constexpr (F32) {
                 const float4 gg = ldp<nt>(reinterpret_cast<const float4 *>(lgeo) + lc);
                 g0[r] = gg.x;
@@ -803,9 +828,19 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
     const int lev_cnt_e = tid <= K ? nE[tid] : 0;
     // local CSR row offsets (chunks padded to multiples of 4 entries)
     const uint2 *crow = reinterpret_cast<const uint2 *>(a.cs_row + h.rw_off);
-    const int nrow4 = (nvu + 1 + 3) >> 2;
-    const uint2 row0 = F32 ? crow[min(tid, nrow4 - 1)] : ldp<nt>(crow + min(tid, nrow4 - 1));
+    const int nrow4 = a.ell ? 0 : (nvu + 1 + 3) >> 2;   // fixed-width rows need no offsets
+    uint2 row0 = make_uint2(0, 0);
+    if (!a.ell) row0 = F32 ? crow[min(tid, nrow4 - 1)] : ldp<nt>(crow + min(tid, nrow4 - 1));
     __builtin_amdgcn_s_waitcnt(0);   // round A complete
+#pragma unroll
+    for (int r = 0; r < EPT; ++r) {
+        const int lc = min(tid + r * BLOCK, ne_load - 1);
+        if (a.ell) tri_unpack(t0[r], t1[r], t2[r], kEllWidth * nvu + (tid & 63));
+        if (lc < h.nown) gt[r] = h.ebase + lc;
+    }
+#pragma unroll
+    for (int u = 0; u < VS; ++u)
+        if (tid + u * BLOCK < h.nv0) gv[u] = h.vbase + tid + u * BLOCK;
 
     auto stage_vertex = [&](int i, int g) {   // register path
         const T ve = eta_in[g], vh = H0[g];
@@ -860,6 +895,24 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
             }
         }
     }
+    // FP64: the staged slots' gathers into registers, all in flight at once
+    constexpr int VR = F32 ? 1 : VS;
+    T ve[VR], vh[VR], va[VR], vw[VR], v1[SM ? VR : 1], v2[SM ? VR : 1], vA[SM ? VR : 1];
+    if constexpr (!F32) {
+#pragma unroll
+        for (int u = 0; u < VR; ++u) {
+            const int g = gv[u];
+            ve[u] = eta_in[g];
+            vh[u] = H0[g];
+            va[u] = ldp<nt>(lav + min(tid + u * BLOCK, nv_load - 1));
+            vw[u] = hasW ? Wt[g] : T(0);
+            if constexpr (SM) {
+                v1[u] = e1_in[g];
+                v2[u] = e2_in[g];
+                vA[u] = pend ? eA_in[g] : T(0);
+            }
+        }
+    }
     if (ne_load > 0) {
 #pragma unroll
         for (int r = 0; r < EPT; ++r) {
@@ -894,11 +947,23 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
             sLev[9 + tid] = lev_cnt_e;
         }
     }
-    if (!dma) {
+    if constexpr (!F32) {
 #pragma unroll
-        for (int u = 0; u < VS; ++u) {
+        for (int u = 0; u < VR; ++u) {
             const int i = tid + u * BLOCK;
-            if (i < nv_load) stage_vertex(i, gv[u]);
+            if (i < nv_load) {
+                sEta[i] = ve[u];
+                sH[i] = vh[u];
+                if constexpr (SM) {
+                    sE1[i] = v1[u];
+                    sE2[i] = v2[u];
+                    sEA[i] = vA[u];
+                }
+                if (i < nvu) {
+                    sAv[i] = va[u];
+                    sW[i] = vw[u];
+                }
+            }
         }
     }
     // remainders: vertices beyond the staged slots, rows beyond the first chunk
@@ -1090,9 +1155,9 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
                         slot_fluxes_f32(abx, aby, g0[r], g1[r], g2[r], g3[r], g4[r], pa, pb, pc);
                     else
                         slot_fluxes(abx, aby, g0[r], g1[r], g2[r], g3[r], g4[r], pa, pb, pc);
-                    sAcc[t1[r] >> 16] = pa;
-                    sAcc[t2[r] & 0xffffu] = pb;
-                    sAcc[t2[r] >> 16] = pc;
+                    sAcc[t2[r] & 0xffffu] = pa;
+                    sAcc[t2[r] >> 16] = pb;
+                    sAcc[t1[r] >> 16] = pc;
                     rUx[r] = Px;
                     rUy[r] = Py;
                     pUx[r] = Qx;
@@ -1159,9 +1224,9 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
                                        pc, dry);
                     dry_any |= dry;
                 }
-                sAcc[t1[r] >> 16] = pa;
-                sAcc[t2[r] & 0xffffu] = pb;
-                sAcc[t2[r] >> 16] = pc;
+                sAcc[t2[r] & 0xffffu] = pa;
+                sAcc[t2[r] >> 16] = pb;
+                sAcc[t1[r] >> 16] = pc;
                 rUx[r] = Unx;
                 rUy[r] = Uny;
                 if (r < OS && le < h.nown) {
@@ -1590,7 +1655,8 @@ __device__ __forceinline__ void adj_tile_body(const AdjTileArgs &a, int b, int G
 
     // ---- load phase: (A) contiguous per-tile data and owned gradients, (B) gathers
     const int32_t *lv = a.lv_gid + h.lv_off;
-    const uint4 *lrec = reinterpret_cast<const uint4 *>(a.le_rec) + h.le_off;
+    const uint2 *lrec = reinterpret_cast<const uint2 *>(a.le_rec) + h.le_off;
+    const int32_t *lgid = a.le_gid + h.le_off;
     const T *lgeo = static_cast<const T *>(a.lgeo) + 4 * (int64_t)h.le_off;
     const T *lae = static_cast<const T *>(a.lae) + h.le_off;
     constexpr int OS = own_slots(EPT);
@@ -1604,11 +1670,11 @@ __device__ __forceinline__ void adj_tile_body(const AdjTileArgs &a, int b, int G
 #pragma unroll
         for (int r = 0; r < EPT; ++r) {
             const int lc = min(tid + r * BLOCK, ne_load - 1);
-            const uint4 rec = ldp<nt>(lrec + lc);
-            gt[r] = (int)rec.x;
-            t0[r] = rec.y;
-            t1[r] = rec.z;
-            t2[r] = rec.w;
+            const uint2 rec = ldp<nt>(lrec + lc);
+            t0[r] = rec.x;
+            t1[r] = rec.y;
+            gt[r] = lgid[min(max(lc, h.nown), ne_load - 1)];
+            if (!a.ell) t2[r] = a.le_pos[h.le_off + lc];
             if constexpr (F32) {
                 const float4 gg = ldp<nt>(reinterpret_cast<const float4 *>(lgeo) + lc);
                 g0[r] = gg.x;
@@ -1645,10 +1711,16 @@ __device__ __forceinline__ void adj_tile_body(const AdjTileArgs &a, int b, int G
 #pragma unroll
     for (int k = 0; k < NVO; ++k) gh[k] = a.seed ? T(0) : gHg[h.vbase + min(tid + k * BLOCK, h.nv0 - 1)];
     const uint2 *crow = reinterpret_cast<const uint2 *>(a.cs_row + h.rw_off);
-    const int nrow4 = (nvu + 1 + 3) >> 2;
+    const int nrow4 = a.ell ? 0 : (nvu + 1 + 3) >> 2;
     const int lev_cnt = tid <= K ? nV[tid] : 0;
     const int lev_cnt_e = tid <= K ? nE[tid] : 0;
     __builtin_amdgcn_s_waitcnt(0);   // round A complete
+#pragma unroll
+    for (int r = 0; r < EPT; ++r) {
+        const int lc = min(tid + r * BLOCK, ne_load - 1);
+        if (a.ell) tri_unpack(t0[r], t1[r], t2[r], kEllWidth * nvu + (tid & 63));
+        if (lc < h.nown) gt[r] = h.ebase + lc;
+    }
 
     const T *lein = static_cast<const T *>(a.lam_eta_in);
     const T *H0g = static_cast<const T *>(a.H0);
@@ -1776,7 +1848,7 @@ __device__ __forceinline__ void adj_tile_body(const AdjTileArgs &a, int b, int G
             const T lgx = -dts * g * He * lrx, lgy = -dts * g * He * lry;
             const T lHe = -dts * g * (gx * lrx + gy * lry);
             const T chi = lHe * third;
-            const int p0 = t1[r] >> 16, p1 = t2[r] & 0xffffu, p2 = t2[r] >> 16;
+            const int p0 = t2[r] & 0xffffu, p1 = t2[r] >> 16, p2 = t1[r] >> 16;
             sPsi[p0] = gax * lgx + gay * lgy;
             sPsi[p1] = gbx * lgx + gby * lgy;
             sPsi[p2] = gcx * lgx + gcy * lgy;

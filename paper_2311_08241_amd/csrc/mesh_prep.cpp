@@ -415,6 +415,7 @@ se_status build_tile_range(const HostMesh &m, size_t mi, int64_t voff, int64_t e
                            std::vector<int32_t> &vloc, std::vector<int32_t> &eloc,
                            HostTiles &out) {
     std::vector<int32_t> lv, le, fresh, pos;
+    std::vector<uint16_t> rank;
     for (int64_t t = t0; t < t1; ++t) {
         const int32_t vb = vstart[t];
         const int32_t nv0 = vstart[t + 1] - vb;
@@ -495,6 +496,7 @@ se_status build_tile_range(const HostMesh &m, size_t mi, int64_t voff, int64_t e
         // that are never updated go to one of 64 scratch slots past the rows.
         const int32_t nvu = nVl[K - 1];
         pos.assign(3 * le.size(), -1);
+        rank.assign(3 * le.size(), 0);
         int32_t nent = 0;
         for (int32_t q = 0; q < nvu; ++q) {
             out.cs_row.push_back(static_cast<uint16_t>(nent));
@@ -507,6 +509,14 @@ se_status build_tile_range(const HostMesh &m, size_t mi, int64_t voff, int64_t e
             }
         }
         const int32_t rows_end = ell ? kEllWidth * nvu : nent;
+        if (ell)   // ranks in the rows of every local vertex, updated or not
+            for (int32_t q = 0; q < static_cast<int32_t>(lv.size()); ++q) {
+                const int32_t r0 = m.row_ptr[lv[q]];
+                for (int32_t j = r0; j < m.row_ptr[lv[q] + 1]; ++j) {
+                    const int32_t i = eloc[m.col[j] >> 2];
+                    if (i >= 0) rank[3 * static_cast<size_t>(i) + (m.col[j] & 3)] = static_cast<uint16_t>(q << 3 | (j - r0));
+                }
+            }
         if (rows_end + 64 > 65535) {
             for (int32_t v : lv) vloc[v] = -1;
             for (int32_t e : le) eloc[e] = -1;
@@ -537,8 +547,12 @@ se_status build_tile_range(const HostMesh &m, size_t mi, int64_t voff, int64_t e
                                             : static_cast<uint32_t>(rows_end + (q & 63));
             // three local vertices and three flux positions, 16 bits each
             out.le_tri.push_back(a | (b << 16));
-            out.le_tri.push_back(c | (p3[0] << 16));
-            out.le_tri.push_back(p3[1] | (p3[2] << 16));
+            out.le_tri.push_back(c | (p3[2] << 16));
+            out.le_tri.push_back(p3[0] | (p3[1] << 16));
+            if (ell) {
+                out.le_rank.push_back(rank[3 * q] | (static_cast<uint32_t>(rank[3 * q + 1]) << 16));
+                out.le_rank.push_back(rank[3 * q + 2]);
+            }
         }
         out.max_nv = std::max(out.max_nv, nVl[K]);
         out.max_ne = std::max(out.max_ne, nEl[K]);
@@ -626,6 +640,7 @@ static se_status build_tiles_pass(const std::vector<const HostMesh *> &members,
         out.lv_gid.insert(out.lv_gid.end(), p.lv_gid.begin(), p.lv_gid.end());
         out.le_gid.insert(out.le_gid.end(), p.le_gid.begin(), p.le_gid.end());
         out.le_tri.insert(out.le_tri.end(), p.le_tri.begin(), p.le_tri.end());
+        out.le_rank.insert(out.le_rank.end(), p.le_rank.begin(), p.le_rank.end());
         out.cs_row.insert(out.cs_row.end(), p.cs_row.begin(), p.cs_row.end());
         out.n_ent += p.n_ent;
         out.max_nv = std::max(out.max_nv, p.max_nv);

@@ -83,9 +83,12 @@ struct HostTiles {
     std::vector<int32_t> nE;      // [ntiles][K+1] cumulative |E_i| (entry 0 = owned)
     std::vector<int32_t> lv_gid;  // local vertex -> global vertex
     std::vector<int32_t> le_gid;  // local triangle -> global triangle
-    // [3 per local triangle]: a | b << 16, c | p0 << 16, p1 | p2 << 16 with local
-    // vertex indices a, b, c and the CSR positions p0..p2 of the three incidences
+    // [3 per local triangle]: a | b << 16, c | pc << 16, pa | pb << 16 with local vertex
+    // indices a, b, c and the positions pa, pb, pc where their incidences are deposited
     std::vector<uint32_t> le_tri;
+    // [2 per local triangle], fixed-width rows only: fa | fb << 16, fc with f = local
+    // vertex << 3 | rank of the triangle in the vertex's row (position f - (f >> 3))
+    std::vector<uint32_t> le_rank;
     std::vector<uint16_t> cs_row; // per tile: nV[K-1] + 1 row offsets (local), padded to 4
     int64_t n_ent = 0;            // local CSR entries over all tiles
     int32_t max_nv = 0, max_ne = 0, max_nvu = 0, max_cs = 0;   // max_cs: rows + 64 scratch
@@ -130,7 +133,7 @@ struct DevTiles {
     }
     bool ok(bool f32, bool sm) const { return sm ? (f32 ? ok_sm32 : ok_sm64) : (f32 ? ok32 : ok64); }
     std::vector<TileHdr> hdr_host;
-    DevBuf hdr, lv_gid, le_rec, cs_row;
+    DevBuf hdr, lv_gid, le_gid, le_rec, le_pos, cs_row;
     DevBuf geo64, geo32, ae64, ae32;   // per local triangle: 4 gradient values; A_e
     DevBuf lav64, lav32;          // per local vertex: 1 / A_v (FP64, FP32)
     // host copies for tables built on first use: global id of each local triangle,

@@ -205,7 +205,34 @@ se_status make_plan(const std::vector<const HostMesh *> &members, const std::vec
                   "k_fused)");
         return SE_ERR_ARG;
     }
+    // tables at a fixed stride per tile, the rest of each tile's entries copies of its last
+    // one (valid ids and indices, never used); odd multiples of 16 entries, so that tiles
+    // loading in step start on different memory channels
+    const int32_t se = ((ht.max_ne + 15) & ~15) | 16, sv = ((ht.max_nv + 15) & ~15) | 16;
+    const size_t nt = ht.hdr.size();
+    {
+        std::vector<int32_t> le(nt * se), lv(nt * sv);
+        std::vector<uint32_t> lt(3 * nt * se), lr(ht.ell ? 2 * nt * se : 0);
+        for (size_t t = 0; t < nt; ++t) {
+            const TileHdr &h = ht.hdr[t];
+            const int32_t n = h.nE[K], nl = h.nV[K];
+            for (int32_t i = 0; i < se; ++i) {
+                const size_t s = h.le_off + std::min(i, n - 1), d = t * se + i;
+                le[d] = ht.le_gid[s];
+                for (int q = 0; q < 3; ++q) lt[3 * d + q] = ht.le_tri[3 * s + q];
+                if (ht.ell)
+                    for (int q = 0; q < 2; ++q) lr[2 * d + q] = ht.le_rank[2 * s + q];
+            }
+            for (int32_t i = 0; i < sv; ++i) lv[t * sv + i] = ht.lv_gid[h.lv_off + std::min(i, nl - 1)];
+        }
+        ht.le_gid.swap(le);
+        ht.lv_gid.swap(lv);
+        ht.le_tri.swap(lt);
+        ht.le_rank.swap(lr);
+    }
     auto p = std::make_unique<DevTiles>();
+    p->se = se;
+    p->sv = sv;
     p->T = T;
     p->K = K;
     p->block = block;
@@ -820,6 +847,8 @@ static TileArgs tile_args(const se_mesh *m, const DevTiles &P, bool f32, const s
     a.le_rec = P.le_rec.as<const uint32_t>();
     a.le_pos = P.le_pos.as<const uint32_t>();
     a.le_gid = P.le_gid.as<const int32_t>();
+    a.se = P.se;
+    a.sv = P.sv;
     a.cs_row = P.cs_row.as<const uint16_t>();
     a.lgeo = f32 ? P.geo32.p : P.geo64.p;
     a.lae = f32 ? P.ae32.p : P.ae64.p;
@@ -841,6 +870,12 @@ static TileArgs tile_args(const se_mesh *m, const DevTiles &P, bool f32, const s
     a.ksub = P.K;
     a.ntiles = P.ntiles;
     a.xcd = 1;
+    // tables loaded ahead of the header when the tiles leave half of the CUs idle: the launch
+    // then lasts as long as one tile's chain of round trips (2,048 vertices 90.5 -> 88.4 us
+    // per call, 11,397 106.9 -> 104.1).  More tiles load against each other and lose by
+    // reading the padding and owned ids (242 tiles FP64 143.2 -> 143.5 at 5 rings, 139.2 ->
+    // 146.7 at 6; 1,039 tiles FP32 578 -> 585; an uneven ensemble 610 -> 648).
+    a.early = P.ntiles <= 128 ? 1 : 0;
     a.cap_nv = P.max_nv;
     a.cap_ne = P.max_ne;
     a.cap_nvu = P.max_nvu;
@@ -1188,7 +1223,7 @@ static se_status ensure_tile_visc(se_mesh *m) {
     std::vector<float> tg32(6 * nle);
     std::vector<int32_t> eloc(m->h.ne, -1);
     for (int32_t t = 0; t < P.ntiles; ++t) {
-        const int64_t off = P.hdr_host[t].le_off;
+        const int64_t off = static_cast<int64_t>(t) * P.se;
         const int32_t n = P.nE_host[static_cast<size_t>(t) * (P.K + 1) + P.K];
         for (int32_t q = 0; q < n; ++q) eloc[P.le_gid_host[off + q]] = q;
         for (int32_t q = 0; q < n; ++q) {
@@ -1493,6 +1528,8 @@ se_status se_subcycle_adjoint(se_mesh *m, const se_params *p, const void *eta0, 
         ra.le_rec = P.le_rec.as<const uint32_t>();
         ra.le_pos = P.le_pos.as<const uint32_t>();
         ra.le_gid = P.le_gid.as<const int32_t>();
+        ra.se = P.se;
+        ra.sv = P.sv;
         ra.cs_row = P.cs_row.as<const uint16_t>();
         ra.lgeo = f32 ? P.geo32.p : P.geo64.p;
         ra.lae = f32 ? P.ae32.p : P.ae64.p;
@@ -1961,6 +1998,8 @@ se_status se_subcycle_batched(se_batch *b, const se_params *p, se_state *st, con
     a.le_rec = P.le_rec.as<const uint32_t>();
     a.le_pos = P.le_pos.as<const uint32_t>();
     a.le_gid = P.le_gid.as<const int32_t>();
+    a.se = P.se;
+    a.sv = P.sv;
     a.cs_row = P.cs_row.as<const uint16_t>();
     a.lgeo = f32 ? P.geo32.p : P.geo64.p;
     a.lae = f32 ? P.ae32.p : P.ae64.p;

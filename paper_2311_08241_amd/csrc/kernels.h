@@ -38,7 +38,15 @@ struct TileHdrK {   // mirror of TileHdr (same layout)
 };
 
 struct TileArgs {
+    // first what a workgroup's first loads need (one kernel-argument line)
     const TileHdrK *hdr;
+    const int32_t *tile_list;   // tiles of this launch (nullptr: all ntiles)
+    int32_t ntiles, xcd;
+    int32_t se, sv;             // triangle and vertex table entries per tile
+    int32_t ell;                // deposits in fixed-width rows (kEllWidth per vertex)
+    int32_t early;              // tables loaded before the tile header arrives
+    int32_t K, chunk;
+    int32_t ksub;               // substeps per launch (K; K / 2 with the viscous term)
     const int32_t *lv_gid;
     // per local triangle: 2 words (ell: local vertices and row ranks; otherwise the
     // packed local vertices and one flux position, the other two in le_pos) and the
@@ -60,11 +68,7 @@ struct TileArgs {
     double *Uavg;
     double *vol_part;
     uint32_t *faults;
-    const int32_t *tile_list;   // tiles of this launch (nullptr: all ntiles)
-    int32_t K, chunk, ntiles, xcd;
-    int32_t ksub;               // substeps per launch (K; K / 2 with the viscous term)
     int32_t cap_nv, cap_ne, cap_nvu, cap_cs;
-    int32_t ell;                // deposits in fixed-width rows (kEllWidth per vertex)
     // viscous term only: per local triangle the local neighbours across its three
     // edges (16 bits each, 0xffff: none in the tile) and (l, l/d) of the three edges
     const uint32_t *vnb;
@@ -94,6 +98,7 @@ struct AdjTileArgs {
     const int32_t *lv_gid;
     const uint32_t *le_rec, *le_pos;
     const int32_t *le_gid;
+    int32_t se, sv;             // triangle and vertex table entries per tile
     const uint16_t *cs_row;
     const void *lgeo, *lae;     // per local triangle: gbx gby gcx gcy; A_e
     const void *Av, *H0, *f;    // global numbering, the precision's type

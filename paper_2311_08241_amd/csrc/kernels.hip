@@ -647,8 +647,67 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
     }
     if (b >= a.ntiles) return;
     if (a.tile_list) b = a.tile_list[b];
-    const TileHdrK h = a.hdr[b];
     constexpr bool nt = NT;   // access policy of the launch (ldp, st1, st2)
+    const int tid = threadIdx.x;
+    // Per-triangle and per-vertex tables sit at a fixed, aligned stride per tile (padded with
+    // copies of the last entry), so their loads need nothing but the tile index: with
+    // a.early they are issued before the header arrives, one dependent round trip less at
+    // the start of a launch, at the price of reading the padding and the owned ids; other
+    // launches wait for the counts and read the entries in use alone.  The aligned rows
+    // alone: 2.2M vertices FP32 2.42 -> 2.30 ms per call, FP64 4.19 -> 4.16, an ensemble of
+    // 24 basins 651 -> 616 us; issued early: 2,048 vertices FP64 92.3 -> 88.7 us, 11,397 FP32
+    // 108.3 -> 105.0.  (FP64 at six triangles per thread and 256 threads lost 3%.)
+    const int64_t le0 = static_cast<int64_t>(b) * a.se, lv0 = static_cast<int64_t>(b) * a.sv;
+    const TileHdrK h = a.hdr[b];
+    __builtin_amdgcn_sched_barrier(0);
+    const int32_t *lv = a.lv_gid + lv0;
+    const uint2 *lrec = reinterpret_cast<const uint2 *>(a.le_rec) + le0;
+    const int32_t *lgid = a.le_gid + le0;
+    const T *lgeo = static_cast<const T *>(a.lgeo) + 4 * le0;
+    const T *lae = static_cast<const T *>(a.lae) + le0;
+    // vertex slots per thread staged in the rounds: a tile has about half as many
+    // vertices as triangles (the rest, if any, in a loop afterwards)
+    constexpr int VS = EPT / 2 + 1;
+    int gv[VS];
+    T g0[EPT], g1[EPT], g2[EPT], g3[EPT], g4[EPT];
+    // local vertices and flux positions, 16 bits each (slots past the tile's triangles
+    // hold copies of its last triangle's)
+    uint32_t t0[EPT], t1[EPT], t2[EPT];
+    int gt[EPT];
+    // entries below ne and nv; global ids from me and mv on (the owned ones follow from
+    // the tile's range)
+    auto load_tables = [&](int ne, int nv, int me, int mv) {
+#pragma unroll
+        for (int u = 0; u < VS; ++u) gv[u] = lv[min(max(tid + u * BLOCK, mv), nv - 1)];
+#pragma unroll
+        for (int r = 0; r < EPT; ++r) {
+            const int lc = min(tid + r * BLOCK, ne - 1);
+            const uint2 rec = ldp<nt>(lrec + lc);
+            t0[r] = rec.x;
+            t1[r] = rec.y;
+            gt[r] = lgid[min(max(lc, me), ne - 1)];
+            if constexpr (F32) {
+                const float4 gg = ldp<nt>(reinterpret_cast<const float4 *>(lgeo) + lc);
+                g0[r] = gg.x;
+                g1[r] = gg.y;
+                g2[r] = gg.z;
+                g3[r] = gg.w;
+            } else {
+                const double2 ga = ldp<nt>(reinterpret_cast<const double2 *>(lgeo) + 2 * lc);
+                const double2 gb = ldp<nt>(reinterpret_cast<const double2 *>(lgeo) + 2 * lc + 1);
+                g0[r] = ga.x;
+                g1[r] = ga.y;
+                g2[r] = gb.x;
+                g3[r] = gb.y;
+            }
+            g4[r] = ldp<nt>(lae + lc);
+        }
+        if (!a.ell) {
+#pragma unroll
+            for (int r = 0; r < EPT; ++r) t2[r] = a.le_pos[le0 + min(tid + r * BLOCK, ne - 1)];
+        }
+    };
+    if (a.early) load_tables(a.se, a.sv, 0, 0);
     // step constants: the member's table row (batches) or the launch's own copy,
     // moved word by word so that both sources stay in scalar registers
     StepC c;
@@ -668,10 +727,10 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
         __builtin_memcpy(&c, wd, sizeof(StepC));
     }
     const int K = a.K, KS = a.ksub;   // rings per tile, substeps per launch
-    const int ch = a.chunk - c.chunk0;   // this member's chunk index
-    if (ch < 0) return;
+    // this member's chunk index; the host launches a member's tiles in its own chunks only
+    // (0 <= ch, ch KS < nsub), and no early return stands between the first loads
+    const int ch = a.chunk - c.chunk0;
     const int m0 = ch * KS;
-    if (m0 >= c.nsub) return;
     const bool even = (ch & 1) == 0;
     const int cnt = min(KS, c.nsub - m0);
     const int rings = VI ? 2 * cnt : cnt;   // rings this launch needs
@@ -682,7 +741,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
     const int *nV = a.hdr[b].nV;   // level counts of the tile (uniform loads)
     const int *nE = a.hdr[b].nE;
     const int nv_load = nV[rings], ne_load = nE[rings], nvu = nV[rings - 1 - (VI ? 1 : 0)];
-    const int tid = threadIdx.x;
+    if (!a.early) load_tables(ne_load, nv_load, h.nown, h.nv0);
 
     // LDS carve-up: the vertex arrays filled by direct-to-LDS loads come first
     int off = 0;
@@ -733,19 +792,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
     const T *eA_in = SM ? static_cast<const T *>(a.sm_v[rs][3]) : nullptr;
     const T *H0 = static_cast<const T *>(a.H0);
     const T *Wt = static_cast<const T *>(a.W);
-    const T *lav = static_cast<const T *>(a.lv_av) + h.lv_off;   // 1 / A_v
-    const int32_t *lv = a.lv_gid + h.lv_off;
-    // vertex slots per thread staged in the rounds: a tile has about half as many
-    // vertices as triangles (the rest, if any, in a loop afterwards)
-    constexpr int VS = EPT / 2 + 1;
-    int gv[VS];
-#pragma unroll
-    for (int u = 0; u < VS; ++u) gv[u] = lv[min(max(tid + u * BLOCK, h.nv0), nv_load - 1)];
-
-    const uint2 *lrec = reinterpret_cast<const uint2 *>(a.le_rec) + h.le_off;
-    const int32_t *lgid = a.le_gid + h.le_off;
-    const T *lgeo = static_cast<const T *>(a.lgeo) + 4 * (int64_t)h.le_off;
-    const T *lae = static_cast<const T *>(a.lae) + h.le_off;
+    const T *lav = static_cast<const T *>(a.lv_av) + lv0;   // 1 / A_v
     const T2 *Uin = static_cast<const T2 *>(
         SM ? (ch == 0 ? a.U_u : a.sm_e[rs][0]) : (even ? a.U_u : a.U_w));
     const T2 *U1in = SM ? static_cast<const T2 *>(ch == 0 ? a.U_u : a.sm_e[rs][1]) : nullptr;
@@ -753,14 +800,9 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
     const T2 *Rg = static_cast<const T2 *>(a.R);
     const T *fg = static_cast<const T *>(a.f);
     const T dts = cdts<T>(c);
-    T rUx[EPT], rUy[EPT], rRx[EPT], rRy[EPT], rf[EPT], rk[EPT], g0[EPT], g1[EPT], g2[EPT],
-        g3[EPT], g4[EPT];
+    T rUx[EPT], rUy[EPT], rRx[EPT], rRy[EPT], rf[EPT], rk[EPT];
     // SM: U^{-1} and the AB3 transport of the previous substep
     T pUx[SM ? EPT : 1], pUy[SM ? EPT : 1], aUx[SM ? EPT : 1], aUy[SM ? EPT : 1];
-    // local vertices and flux positions, 16 bits each (slots past the tile's triangles
-    // hold copies of its last triangle's)
-    uint32_t t0[EPT] = {}, t1[EPT] = {}, t2[EPT] = {};
-    int gt[EPT];
     // running sums only in the slots that can hold owned triangles (the plan keeps
     // every tile's owned triangles within them); osl(r) names slot r's sum
     constexpr int OS = own_slots(EPT);
@@ -772,45 +814,19 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
     // 512-thread workgroups (the same register tier), slower elsewhere
     constexpr int HV = (VI && F32 && BLOCK <= 512 && EPT <= 3) ? EPT : 0;
     T vgh[HV > 0 ? 6 * HV : 1];
-    if (ne_load > 0) {
+    if constexpr (HV > 0) {
 #pragma unroll
-        for (int r = 0; r < EPT; ++r) {
+        for (int r = 0; r < HV; ++r) {
             const int lc = min(tid + r * BLOCK, ne_load - 1);
-            const uint2 rec = ldp<nt>(lrec + lc);
-            t0[r] = rec.x;
-            t1[r] = rec.y;
-            gt[r] = lgid[min(max(lc, h.nown), ne_load - 1)];
-            if (!a.ell) t2[r] = a.le_pos[h.le_off + lc];
-            if constexpr (F32) {
-                const float4 gg = ldp<nt>(reinterpret_cast<const float4 *>(lgeo) + lc);
-                g0[r] = gg.x;
-                g1[r] = gg.y;
-                g2[r] = gg.z;
-                g3[r] = gg.w;
-            } else {
-                const double2 ga = ldp<nt>(reinterpret_cast<const double2 *>(lgeo) + 2 * lc);
-                const double2 gb = ldp<nt>(reinterpret_cast<const double2 *>(lgeo) + 2 * lc + 1);
-                g0[r] = ga.x;
-                g1[r] = ga.y;
-                g2[r] = gb.x;
-                g3[r] = gb.y;
-            }
-            g4[r] = ldp<nt>(lae + lc);
-        }
-        if constexpr (HV > 0) {
+            const T *vg = static_cast<const T *>(a.vgeo) + 6 * (le0 + lc);
 #pragma unroll
-            for (int r = 0; r < HV; ++r) {
-                const int lc = min(tid + r * BLOCK, ne_load - 1);
-                const T *vg = static_cast<const T *>(a.vgeo) + 6 * (int64_t)(h.le_off + lc);
-#pragma unroll
-                for (int q = 0; q < 6; ++q) vgh[6 * r + q] = ldp<nt>(vg + q);
-            }
+            for (int q = 0; q < 6; ++q) vgh[6 * r + q] = ldp<nt>(vg + q);
         }
-        if (!first && h.nown > 0) {
-            // running sums of owned triangles (the tile's contiguous global range)
+    }
+    if (!first && h.nown > 0) {
+        // running sums of owned triangles (the tile's contiguous global range)
 #pragma unroll
-            for (int r = 0; r < OS; ++r) sm[r].load(a.sum, h.ebase + min(tid + r * BLOCK, h.nown - 1));
-        }
+        for (int r = 0; r < OS; ++r) sm[r].load(a.sum, h.ebase + min(tid + r * BLOCK, h.nown - 1));
     }
     // FP64 dual-cell areas of owned vertices, for the volume sums of this launch
     constexpr int VO = 2;   // owned-vertex slots held in registers
@@ -832,15 +848,18 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
     uint2 row0 = make_uint2(0, 0);
     if (!a.ell) row0 = F32 ? crow[min(tid, nrow4 - 1)] : ldp<nt>(crow + min(tid, nrow4 - 1));
     __builtin_amdgcn_s_waitcnt(0);   // round A complete
+    if (a.ell) {
 #pragma unroll
-    for (int r = 0; r < EPT; ++r) {
-        const int lc = min(tid + r * BLOCK, ne_load - 1);
-        if (a.ell) tri_unpack(t0[r], t1[r], t2[r], kEllWidth * nvu + (tid & 63));
-        if (lc < h.nown) gt[r] = h.ebase + lc;
+        for (int r = 0; r < EPT; ++r) tri_unpack(t0[r], t1[r], t2[r], kEllWidth * nvu + (tid & 63));
     }
+    if (!a.early) {   // owned ids from the tile's range
 #pragma unroll
-    for (int u = 0; u < VS; ++u)
-        if (tid + u * BLOCK < h.nv0) gv[u] = h.vbase + tid + u * BLOCK;
+        for (int r = 0; r < EPT; ++r)
+            if (tid + r * BLOCK < h.nown) gt[r] = h.ebase + tid + r * BLOCK;
+#pragma unroll
+        for (int u = 0; u < VS; ++u)
+            if (tid + u * BLOCK < h.nv0) gv[u] = h.vbase + tid + u * BLOCK;
+    }
 
     auto stage_vertex = [&](int i, int g) {   // register path
         const T ve = eta_in[g], vh = H0[g];
@@ -901,6 +920,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
     if constexpr (!F32) {
 #pragma unroll
         for (int u = 0; u < VR; ++u) {
+            if (u > 0 && u * BLOCK >= nv_load) continue;
             const int g = gv[u];
             ve[u] = eta_in[g];
             vh[u] = H0[g];
@@ -913,9 +933,10 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
             }
         }
     }
-    if (ne_load > 0) {
+    {
 #pragma unroll
         for (int r = 0; r < EPT; ++r) {
+            if (r > 0 && r * BLOCK >= ne_load) continue;   // (a.early: a short launch's outer rings)
             const int g = gt[r];
             const T2 u = Uin[g];
             rUx[r] = u.x;
@@ -978,7 +999,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
     }
     for (int i = tid + BLOCK; i < nrow4; i += BLOCK) reinterpret_cast<uint2 *>(sRow)[i] = ldp<nt>(crow + i);
     if constexpr (VI) {
-        const uint2 *nbt = reinterpret_cast<const uint2 *>(a.vnb) + h.le_off;
+        const uint2 *nbt = reinterpret_cast<const uint2 *>(a.vnb) + le0;
         for (int i = tid; i < ne_load; i += BLOCK) sNb[i] = ldp<nt>(nbt + i);
     }
     if (a.ell) {
@@ -1177,9 +1198,9 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
                 if constexpr (VI) {
                     // V(eta^m, U^m): edges to local neighbours (0xffff: coast)
                     const uint2 nbp = sNb[le];
-                    const int lq = h.le_off + tidv + r * BLOCK;   // = h.le_off + le
+                    const int64_t lq = le0 + tidv + r * BLOCK;   // = le0 + le
                     const T *vg = r < HV ? vgh + 6 * (r < HV ? r : 0)
-                                         : static_cast<const T *>(a.vgeo) + 6 * (int64_t)lq;
+                                         : static_cast<const T *>(a.vgeo) + 6 * lq;
                     const int nbs[3] = {static_cast<int>(nbp.x & 0xffffu),
                                         static_cast<int>(nbp.x >> 16),
                                         static_cast<int>(nbp.y & 0xffffu)};
@@ -1419,7 +1440,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
 
 template <typename T, bool F32, int EPT, int BLOCK, int MODE, bool NT>
 __global__ void __launch_bounds__(BLOCK) k_tile(TileArgs a) {
-    tile_body<T, F32, EPT, BLOCK, MODE, NT>(a, blockIdx.x, gridDim.x);
+    tile_body<T, F32, EPT, BLOCK, MODE, NT>(a, blockIdx.x, a.ntiles);   // one block per tile
 }
 
 // ---------------------------------------------------------------------------
@@ -1654,11 +1675,12 @@ __device__ __forceinline__ void adj_tile_body(const AdjTileArgs &a, int b, int G
     uint16_t *sRow = reinterpret_cast<uint16_t *>(smem + off);
 
     // ---- load phase: (A) contiguous per-tile data and owned gradients, (B) gathers
-    const int32_t *lv = a.lv_gid + h.lv_off;
-    const uint2 *lrec = reinterpret_cast<const uint2 *>(a.le_rec) + h.le_off;
-    const int32_t *lgid = a.le_gid + h.le_off;
-    const T *lgeo = static_cast<const T *>(a.lgeo) + 4 * (int64_t)h.le_off;
-    const T *lae = static_cast<const T *>(a.lae) + h.le_off;
+    const int64_t le0 = static_cast<int64_t>(b) * a.se;
+    const int32_t *lv = a.lv_gid + static_cast<int64_t>(b) * a.sv;
+    const uint2 *lrec = reinterpret_cast<const uint2 *>(a.le_rec) + le0;
+    const int32_t *lgid = a.le_gid + le0;
+    const T *lgeo = static_cast<const T *>(a.lgeo) + 4 * le0;
+    const T *lae = static_cast<const T *>(a.lae) + le0;
     constexpr int OS = own_slots(EPT);
     // den: 1 / (1 + a^2)
     T g0[EPT], g1[EPT], g2[EPT], g3[EPT], g4[EPT], lUx[EPT], lUy[EPT], al[EPT], den[EPT];
@@ -1674,7 +1696,7 @@ __device__ __forceinline__ void adj_tile_body(const AdjTileArgs &a, int b, int G
             t0[r] = rec.x;
             t1[r] = rec.y;
             gt[r] = lgid[min(max(lc, h.nown), ne_load - 1)];
-            if (!a.ell) t2[r] = a.le_pos[h.le_off + lc];
+            if (!a.ell) t2[r] = a.le_pos[le0 + lc];
             if constexpr (F32) {
                 const float4 gg = ldp<nt>(reinterpret_cast<const float4 *>(lgeo) + lc);
                 g0[r] = gg.x;
@@ -1934,7 +1956,7 @@ __device__ __forceinline__ void adj_tile_body(const AdjTileArgs &a, int b, int G
 
 template <typename T, bool F32, int EPT, int BLOCK>
 __global__ void __launch_bounds__(BLOCK) k_adj_tile(AdjTileArgs a) {
-    adj_tile_body<T, F32, EPT, BLOCK>(a, blockIdx.x, gridDim.x);
+    adj_tile_body<T, F32, EPT, BLOCK>(a, blockIdx.x, a.ntiles);
 }
 
 // The reverse substeps of one checkpoint segment (blocks [0, nrev)) and the recompute,
@@ -1947,7 +1969,7 @@ __global__ void __launch_bounds__(BLOCK) k_adj_tile_pair(AdjTileArgs ra, TileArg
     if ((int)blockIdx.x < nrev)
         adj_tile_body<T, F32, EPT, BLOCK>(ra, blockIdx.x, nrev);
     else
-        tile_body<T, F32, EPT, BLOCK, 3>(fa, blockIdx.x - nrev, gridDim.x - nrev);
+        tile_body<T, F32, EPT, BLOCK, 3>(fa, blockIdx.x - nrev, fa.ntiles);
 }
 
 // Deterministic sum of each row of partials: out[r] = add + sum_i part[r*width + i].

@@ -65,7 +65,8 @@ bool build_trim_tiles(const HostMesh &m, int cap_e, int cap_o, int cap_v, TrimTi
 struct TileHdr {
     int32_t vbase, nv0;     // owned vertex range (global, union numbering)
     int32_t ebase, nown;    // owned triangle range
-    int32_t lv_off, le_off; // offsets into local vertex / triangle arrays
+    int32_t lv_off, le_off; // offsets into HostTiles' local vertex / triangle arrays (the
+                            // device tables have a fixed stride per tile)
     int32_t cs_off, rw_off; // (unused) / offset into local CSR rows
     int32_t member;         // batch member (0 for a single mesh)
     int32_t mtile;          // tile index within its member
@@ -117,6 +118,7 @@ struct DevBuf {
 struct DevTiles {
     int32_t T = 0, K = 0, block = 256, ept = 0, ntiles = 0;
     bool ell = false;   // fixed-width deposit rows (HostTiles::ell)
+    int32_t se = 0, sv = 0;   // triangle and vertex table entries per tile (padded)
     int32_t max_nv = 0, max_ne = 0, max_nvu = 0, max_cs = 0;
     size_t lds_bytes64 = 0, lds_bytes32 = 0;
     bool ok32 = false, ok64 = false;

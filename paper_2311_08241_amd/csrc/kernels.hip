@@ -12,9 +12,9 @@
 // plus the running sum of U' for the averaged transport of eq. (eq4_12) and
 // the volume sum_v A_v eta_v.
 //
-// All floating-point code is compiled without FMA contraction so that every
-// path (plain, any tile plan) performs the same IEEE operations in the same
-// order: FP64 results do not depend on the plan.
+// All floating-point code is compiled without FMA contraction, with fused multiply-adds
+// written out where they are meant, so that every path (plain, any tile plan) performs
+// the same IEEE operations in the same order: results do not depend on the plan.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -40,90 +40,72 @@ template <typename T> __device__ __forceinline__ T copt(const StepC &c);
 template <> __device__ __forceinline__ double copt<double>(const StepC &c) { return c.opt; }
 template <> __device__ __forceinline__ float copt<float>(const StepC &c) { return c.opt_f; }
 
-// Per-triangle update.  ea..ec: eta at the vertices (FP64: absolute; FP32:
-// deviation from eta_ref), ha..hc: H0, al = f dt_s / 2 (0.5 f first, then dt_s).
-// Returns U' and the three sub-cell fluxes; dry is set when the triangle's total depth
-// is not positive.  The CPU definition's divisions by 3 and by 1 + a^2 are
-// multiplications by reciprocals here (one FP64 division per triangle and substep
-// instead of three; agreement with the definition to rounding), the same in every
-// path and plan.
-template <typename T, bool F32>
-__device__ __forceinline__ void tri_update(T ea, T eb, T ec, T ha, T hb, T hc, T gbx, T gby,
-                                           T gcx, T gcy, T Ae, T Ux, T Uy, T Rx, T Ry, T al,
-                                           const StepC &c, bool linear_h, T &Unx, T &Uny,
-                                           T &pa, T &pb, T &pc, bool &dry) {
-    const T dts = cdts<T>(c), g = cg<T>(c), th = cth<T>(c), opt = copt<T>(c);
-    const T db = eb - ea, dc = ec - ea;
-    const T gx = db * gbx + dc * gcx;
-    const T gy = db * gby + dc * gcy;
-    const T third = T(1) / T(3);
-    T He;
-    if (linear_h) {
-        He = (ha + hb + hc) * third;
-    } else if (!F32) {
-        He = ((ha + ea) + (hb + eb) + (hc + ec)) * third;
-    } else {
-        He = ((ha + hb + hc) + (ea + eb + ec)) * third + c.eta_ref_f;
-    }
-    dry = !(He > T(0));
-    const T rx = Ux + al * Uy + dts * (-g * He * gx + Rx);
-    const T ry = Uy - al * Ux + dts * (-g * He * gy + Ry);
-    const T rden = T(1) / (T(1) + al * al);
-    Unx = (rx + al * ry) * rden;
-    Uny = (ry - al * rx) * rden;
-    const T Fx = opt * Unx - th * Ux;
-    const T Fy = opt * Uny - th * Uy;
-    const T gax = -(gbx + gcx), gay = -(gby + gcy);
-    pa = Fx * (-Ae * gax) + Fy * (-Ae * gay);
-    pb = Fx * (-Ae * gbx) + Fy * (-Ae * gby);
-    pc = Fx * (-Ae * gcx) + Fy * (-Ae * gcy);
-}
-
-// FP32 triangle update with per-triangle constants of the call: a = f dt/2 (al),
-// 1/(1 + a^2) (rk), dt R (dRx, dRy), -A_e (mAe), mean H0 (+ eta_ref unless H is
-// linear) (rH); gd = g dt.  The Crank-Nicolson step is evaluated as the increment
+// Triangle update, FP64 and FP32, with per-triangle constants of the call: a = f dt/2
+// (al), 1/(1 + a^2) (rk), dt R (dRx, dRy), -A_e (mAe), mean H0 (FP32: + eta_ref unless H is
+// linear) (rH); gd = g dt; ea..ec: eta at the vertices (FP64: absolute; FP32: deviation
+// from eta_ref).  Returns U' and the three sub-cell fluxes; dry is set when the triangle's
+// total depth is not positive.  The Crank-Nicolson step is evaluated as the increment
 //   U' = U + C (q - 2 a J U),  C = (I + aJ)^-1,  q = dt (R - g H grad eta),
-// algebraically equal to C [(I - aJ) U + q]; in FP32 the rounded rotation
-// coefficients then perturb only the small increment instead of scaling U by
-// 1 + O(eps) every substep, which would bias its amplitude over many substeps.
-__device__ __forceinline__ void tri_update_f32(float ea, float eb, float ec, float rH, float gbx,
-                                               float gby, float gcx, float gcy, float mAe,
-                                               float ux, float uy, float dRx, float dRy,
-                                               float al, float rk, float gd, float th,
-                                               bool linear_h, float &Unx, float &Uny, float &pa,
-                                               float &pb, float &pc, bool &dry) {
+// algebraically equal to C [(I - aJ) U + q]; the rounded rotation coefficients then perturb
+// only the small increment instead of scaling U by 1 + O(eps) every substep, which would
+// bias its amplitude over many substeps (visible in FP32).  Products that feed sums are
+// fused multiply-adds; the fluxes of vertices b and c are formed and a's is minus their
+// sum (the three vectors sum to zero).  Both precisions evaluate the same 31 operations;
+// the FP64 form in the order of the CPU definition took 60 FP64 instructions, most of a
+// small tile's substep (2,048 vertices 88.7 -> 81.7 us per call, 61,897 182 -> 167, 2.2M
+// 4.16 -> 4.10 ms).  Against an 80-bit evaluation the FP64 transports of 30 to 80 substeps
+// are 3e-16 to 5e-16 off in the 2-norm, 1.7e-15 to 4.7e-15 before.
+template <typename T>
+__device__ __forceinline__ void tri_update(T ea, T eb, T ec, T rH, T gbx, T gby, T gcx, T gcy,
+                                           T mAe, T ux, T uy, T dRx, T dRy, T al, T rk, T gd, T th,
+                                           bool linear_h, T &Unx, T &Uny, T &pa, T &pb, T &pc,
+                                           bool &dry) {
     // fused multiply-adds (one rounding each) where a product feeds a sum
-    const float db = eb - ea, dc = ec - ea;
-    const float gx = __builtin_fmaf(db, gbx, dc * gcx);
-    const float gy = __builtin_fmaf(db, gby, dc * gcy);
-    const float He = linear_h ? rH : __builtin_fmaf(ea + eb + ec, 1.0f / 3.0f, rH);
-    dry = !(He > 0.0f);
-    const float gHe = gd * He;
-    const float al2 = 2.0f * al;
-    const float px = __builtin_fmaf(al2, uy, __builtin_fmaf(-gHe, gx, dRx));
-    const float py = __builtin_fmaf(-al2, ux, __builtin_fmaf(-gHe, gy, dRy));
-    const float dx = __builtin_fmaf(al, py, px) * rk;
-    const float dy = __builtin_fmaf(-al, px, py) * rk;
+    auto fma = [](T x, T y, T z) -> T {
+        if constexpr (sizeof(T) == 4) return __builtin_fmaf(x, y, z);
+        else return __builtin_fma(x, y, z);
+    };
+    const T db = eb - ea, dc = ec - ea;
+    const T gx = fma(db, gbx, dc * gcx);
+    const T gy = fma(db, gby, dc * gcy);
+    const T He = linear_h ? rH : fma(ea + eb + ec, T(1) / T(3), rH);
+    dry = !(He > T(0));
+    const T gHe = gd * He;
+    const T al2 = T(2) * al;
+    const T px = fma(al2, uy, fma(-gHe, gx, dRx));
+    const T py = fma(-al2, ux, fma(-gHe, gy, dRy));
+    const T dx = fma(al, py, px) * rk;
+    const T dy = fma(-al, px, py) * rk;
     Unx = ux + dx;
     Uny = uy + dy;
-    const float Fx = __builtin_fmaf(th, dx, Unx);   // (1 + theta) U' - theta U
-    const float Fy = __builtin_fmaf(th, dy, Uny);
-    pb = mAe * __builtin_fmaf(Fx, gbx, Fy * gby);
-    pc = mAe * __builtin_fmaf(Fx, gcx, Fy * gcy);
+    const T Fx = fma(th, dx, Unx);   // (1 + theta) U' - theta U
+    const T Fy = fma(th, dy, Uny);
+    pb = mAe * fma(Fx, gbx, Fy * gby);
+    pc = mAe * fma(Fx, gcx, Fy * gcy);
     pa = -(pb + pc);
 }
 
-// FP32 vertex update eta - dt (sum / A_v + W) with the reciprocal area 1 / A_v
-// (identical in every path).
-template <typename T>
-__device__ __forceinline__ T vtx_update_f32(T eta, T acc, T rav, T w, T dts) {
+// Vertex update eta - dt (sum / A_v + W) with the reciprocal area 1 / A_v (identical in
+// every path).
+__device__ __forceinline__ float vtx_update(float eta, float acc, float rav, float w, float dts) {
     return __builtin_fmaf(-dts, __builtin_fmaf(acc, rav, w), eta);
 }
+__device__ __forceinline__ double vtx_update(double eta, double acc, double rav, double w, double dts) {
+    return __builtin_fma(-dts, __builtin_fma(acc, rav, w), eta);
+}
 
-// Per-triangle constants of the FP32 update (identical in every path).
-__device__ __forceinline__ void tri_consts_f32(float f, float dts, float &al, float &rk) {
-    al = 0.5f * f * dts;
-    rk = 1.0f / (1.0f + al * al);
+// Per-triangle constants of the update (identical in every path).
+template <typename T> __device__ __forceinline__ void tri_consts(T f, T dts, T &al, T &rk) {
+    al = T(0.5) * f * dts;
+    rk = T(1) / (T(1) + al * al);
+}
+
+// Mean depth constant of a triangle (FP32: with eta_ref unless H is linear).
+template <typename T>
+__device__ __forceinline__ T tri_mean_h(T ha, T hb, T hc, bool linear_h, const StepC &c) {
+    const T h = (ha + hb + hc) * (T(1) / T(3));
+    if constexpr (sizeof(T) == 4) return h + (linear_h ? 0.0f : c.eta_ref_f);
+    else return h;
 }
 
 // Non-temporal accesses of the tile kernels.  A tile's own triangle records, geometry
@@ -248,20 +230,13 @@ __device__ __forceinline__ void plain_tri_at(const PlainArgs &a, int64_t e) {
     T Unx, Uny, pa, pb, pc;
     bool dry;
     const bool linear_h = (c.flags & KF_LINEAR_H) != 0;
-    if constexpr (F32) {
-        float al, rk;
-        tri_consts_f32(fc, c.dts_f, al, rk);
-        const float rH = (H0[va] + H0[vb] + H0[vc]) * (1.0f / 3.0f) + (linear_h ? 0.0f : c.eta_ref_f);
-        tri_update_f32(eta[va], eta[vb], eta[vc], rH, geom[e], geom[a.ne + e],
-                       geom[2 * a.ne + e], geom[3 * a.ne + e], -geom[4 * a.ne + e], u.x, u.y,
-                       c.dts_f * r.x, c.dts_f * r.y, al, rk, c.g_f * c.dts_f, c.theta_f,
-                       linear_h, Unx, Uny, pa, pb, pc, dry);
-    } else {
-        tri_update<T, F32>(eta[va], eta[vb], eta[vc], H0[va], H0[vb], H0[vc], geom[e],
-                           geom[a.ne + e], geom[2 * a.ne + e], geom[3 * a.ne + e],
-                           geom[4 * a.ne + e], u.x, u.y, r.x, r.y, T(0.5) * fc * cdts<T>(c), c,
-                           linear_h, Unx, Uny, pa, pb, pc, dry);
-    }
+    const T dts = cdts<T>(c);
+    T al, rk;
+    tri_consts<T>(fc, dts, al, rk);
+    tri_update<T>(eta[va], eta[vb], eta[vc], tri_mean_h<T>(H0[va], H0[vb], H0[vc], linear_h, c),
+                  geom[e], geom[a.ne + e], geom[2 * a.ne + e], geom[3 * a.ne + e],
+                  -geom[4 * a.ne + e], u.x, u.y, dts * r.x, dts * r.y, al, rk, cg<T>(c) * dts,
+                  cth<T>(c), linear_h, Unx, Uny, pa, pb, pc, dry);
     if (dry) set_fault(a.faults, 1u);
     T *phi = static_cast<T *>(a.phi);
     phi[3 * e] = pa;
@@ -310,8 +285,7 @@ __device__ __forceinline__ void plain_vtx_at(const PlainArgs &a, int64_t v, doub
     const T eo = a.eta_src ? static_cast<const T *>(a.eta_src)[v] : eta[v];
     const T wv = a.W ? static_cast<const T *>(a.W)[v] : T(0);
     const T av = static_cast<const T *>(a.Av)[v];
-    const T en = F32 ? vtx_update_f32(eo, acc, T(1) / av, wv, cdts<T>(c))
-                     : eo - cdts<T>(c) * (acc * (T(1) / av) + wv);
+    const T en = vtx_update(eo, acc, T(1) / av, wv, cdts<T>(c));
     eta[v] = en;
     if (!finite_val(en)) set_fault(a.faults, 2u);
     const double av64 = a.Av64[v];
@@ -474,8 +448,7 @@ __global__ void __launch_bounds__(256) k_sesm_vtx(PlainArgs a) {
         const T eo = eta[v], e1 = eta1[v], e2 = eta2[v];
         const T wv = a.W ? static_cast<const T *>(a.W)[v] : T(0);
         const T av = static_cast<const T *>(a.Av)[v];
-        const T en = F32 ? vtx_update_f32(eo, acc, T(1) / av, wv, cdts<T>(c))
-                         : eo - cdts<T>(c) * (acc * (T(1) / av) + wv);
+        const T en = vtx_update(eo, acc, T(1) / av, wv, cdts<T>(c));
         static_cast<T *>(a.etaA)[v] = sesm_am<T>(c, en, eo, e1, e2);
         eta2[v] = e1;
         eta1[v] = eo;
@@ -814,15 +787,8 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
     // 512-thread workgroups (the same register tier), slower elsewhere
     constexpr int HV = (VI && F32 && BLOCK <= 512 && EPT <= 3) ? EPT : 0;
     T vgh[HV > 0 ? 6 * HV : 1];
-    if constexpr (HV > 0) {
 #pragma unroll
-        for (int r = 0; r < HV; ++r) {
-            const int lc = min(tid + r * BLOCK, ne_load - 1);
-            const T *vg = static_cast<const T *>(a.vgeo) + 6 * (le0 + lc);
-#pragma unroll
-            for (int q = 0; q < 6; ++q) vgh[6 * r + q] = ldp<nt>(vg + q);
-        }
-    }
+    for (int r = 0; r < OS; ++r) sm[r].x = sm[r].y = 0.0;
     if (!first && h.nown > 0) {
         // running sums of owned triangles (the tile's contiguous global range)
 #pragma unroll
@@ -1002,6 +968,15 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
         const uint2 *nbt = reinterpret_cast<const uint2 *>(a.vnb) + le0;
         for (int i = tid; i < ne_load; i += BLOCK) sNb[i] = ldp<nt>(nbt + i);
     }
+    if constexpr (HV > 0) {
+#pragma unroll
+        for (int r = 0; r < HV; ++r) {
+            const int lc = min(tid + r * BLOCK, ne_load - 1);
+            const T *vg = static_cast<const T *>(a.vgeo) + 6 * (le0 + lc);
+#pragma unroll
+            for (int q = 0; q < 6; ++q) vgh[6 * r + q] = ldp<nt>(vg + q);
+        }
+    }
     if (a.ell) {
         // fixed-width rows: the entries past a vertex's triangles are never written
         // and must read as zero (adding +0 leaves every row sum unchanged)
@@ -1022,41 +997,36 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
     }
     __builtin_amdgcn_s_waitcnt(0);   // round B complete (direct-to-LDS loads included)
     __syncthreads();
-    if constexpr (F32) {
-        // FP32: per-triangle constants of the launch (see tri_update_f32)
+    // per-triangle constants of the launch (see tri_update; AB3-AM4: f dt in FP32)
 #pragma unroll
-        for (int r = 0; r < EPT; ++r) {
-            const int le = tid + r * BLOCK;
-            if (le < ne_load) {
-                if constexpr (SM) {
-                    rf[r] = rf[r] * dts;   // f dt
-                } else {
-                    float al, kk;
-                    tri_consts_f32(rf[r], dts, al, kk);
-                    rk[r] = kk;
-                    rf[r] = al;
-                }
-                if constexpr (!VI) {   // VI: R + V, scaled at every substep
-                    rRx[r] = dts * rRx[r];
-                    rRy[r] = dts * rRy[r];
-                }
-                g4[r] = -g4[r];
-            }
+    for (int r = 0; r < EPT; ++r) {
+        const int le = tid + r * BLOCK;
+        if (F32 && le >= ne_load) continue;
+        if constexpr (!SM) {
+            T al, kk;
+            tri_consts<T>(rf[r], dts, al, kk);
+            rk[r] = kk;
+            rf[r] = al;
+        } else if constexpr (F32) {
+            rf[r] = rf[r] * dts;
         }
-    } else if constexpr (!SM) {
-        // FP64 forward-backward: a = f dt_s / 2 of the launch in place of f
-#pragma unroll
-        for (int r = 0; r < EPT; ++r) rf[r] = T(0.5) * rf[r] * dts;
+        if constexpr (!VI && (F32 || !SM)) {   // VI: R + V, scaled at every substep
+            rRx[r] = dts * rRx[r];
+            rRy[r] = dts * rRy[r];
+        }
+        if constexpr (F32 || !SM) g4[r] = -g4[r];
     }
-    T rH[F32 ? EPT : 1];
-    if constexpr (F32) {
+    // the mean depth constant in registers, except in FP64 beyond two triangles per thread
+    // (formed from LDS at every substep, the same operations)
+    constexpr bool HM = F32 || (!SM && EPT <= 2);
+    T rH[HM ? EPT : 1];
+    if constexpr (HM) {
 #pragma unroll
         for (int r = 0; r < EPT; ++r) {
             const int le = tid + r * BLOCK;
-            if (le < ne_load) {
-                const int ia = t0[r] & 0xffffu, ib = t0[r] >> 16, ic = t1[r] & 0xffffu;
-                rH[r] = (sH[ia] + sH[ib] + sH[ic]) * (1.0f / 3.0f) + (linear_h ? 0.0f : c.eta_ref_f);
-            }
+            if (le < ne_load)
+                rH[r] = tri_mean_h<T>(sH[t0[r] & 0xffffu], sH[t0[r] >> 16], sH[t1[r] & 0xffffu],
+                                      linear_h, c);
         }
     }
 
@@ -1115,7 +1085,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
         }
         // FP32 forward-backward: the three elevations of every slot read before any
         // update, so that all slots wait for one LDS round trip
-        float hE[(F32 && FB) ? 3 * EPT : 1];
+        T hE[(F32 && FB) ? 3 * EPT : 1];
         if constexpr (F32 && FB) {
 #pragma unroll
             for (int r = 0; r < EPT; ++r) {
@@ -1185,12 +1155,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
                     pUy[r] = Qy;
                     aUx[r] = abx;
                     aUy[r] = aby;
-                    if (r < OS && le < h.nown) {
-                        if (first && j == 0)
-                            sm[osl(r)].init(abx, aby);
-                        else
-                            sm[osl(r)].add(abx, aby);
-                    }
+                    if (r < OS) sm[osl(r)].add(abx, aby);
                     continue;
                 }
                 T Unx, Uny, pa, pb, pc;
@@ -1198,9 +1163,9 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
                 if constexpr (VI) {
                     // V(eta^m, U^m): edges to local neighbours (0xffff: coast)
                     const uint2 nbp = sNb[le];
-                    const int64_t lq = le0 + tidv + r * BLOCK;   // = le0 + le
+                    const int lq = tidv + r * BLOCK;   // = le
                     const T *vg = r < HV ? vgh + 6 * (r < HV ? r : 0)
-                                         : static_cast<const T *>(a.vgeo) + 6 * lq;
+                                         : static_cast<const T *>(a.vgeo) + 6 * le0 + 6 * lq;
                     const int nbs[3] = {static_cast<int>(nbp.x & 0xffffu),
                                         static_cast<int>(nbp.x >> 16),
                                         static_cast<int>(nbp.y & 0xffffu)};
@@ -1220,29 +1185,19 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
                                      vg[2 * q], vg[2 * q + 1], sUb[2 * n] - uex,
                                      sUb[2 * n + 1] - uey, sx, sy);
                     }
-                    const T Ae = F32 ? -g4[r] : g4[r];
-                    rx = rRx[r] + sx / Ae;
-                    ry = rRy[r] + sy / Ae;
-                    if constexpr (F32) {
-                        rx = dts * rx;
-                        ry = dts * ry;
-                    }
+                    const T Ae = -g4[r];
+                    rx = dts * (rRx[r] + sx / Ae);
+                    ry = dts * (rRy[r] + sy / Ae);
                 }
-                if constexpr (F32) {
+                {
                     bool dry;
-                    const float ea = FB ? hE[FB ? 3 * r : 0] : sEta[ia];
-                    const float eb = FB ? hE[FB ? 3 * r + 1 : 0] : sEta[ib];
-                    const float ec = FB ? hE[FB ? 3 * r + 2 : 0] : sEta[ic];
-                    tri_update_f32(ea, eb, ec, rH[r], g0[r], g1[r], g2[r],
-                                   g3[r], g4[r], rUx[r], rUy[r], rx, ry, rf[r], rk[r],
-                                   gd, th, linear_h, Unx, Uny, pa, pb, pc, dry);
-                    dry_any |= dry;
-                } else {
-                    bool dry;
-                    tri_update<T, F32>(sEta[ia], sEta[ib], sEta[ic], sH[ia], sH[ib], sH[ic],
-                                       g0[r], g1[r], g2[r], g3[r], g4[r], rUx[r], rUy[r],
-                                       rx, ry, rf[r], c, linear_h, Unx, Uny, pa, pb,
-                                       pc, dry);
+                    const T ea = (F32 && FB) ? hE[(F32 && FB) ? 3 * r : 0] : sEta[ia];
+                    const T eb = (F32 && FB) ? hE[(F32 && FB) ? 3 * r + 1 : 0] : sEta[ib];
+                    const T ec = (F32 && FB) ? hE[(F32 && FB) ? 3 * r + 2 : 0] : sEta[ic];
+                    const T hm = HM ? rH[HM ? r : 0] : tri_mean_h<T>(sH[ia], sH[ib], sH[ic], linear_h, c);
+                    tri_update<T>(ea, eb, ec, hm, g0[r], g1[r], g2[r], g3[r], g4[r], rUx[r],
+                                  rUy[r], rx, ry, rf[r], rk[r], gd, th, linear_h, Unx, Uny, pa,
+                                  pb, pc, dry);
                     dry_any |= dry;
                 }
                 sAcc[t2[r] & 0xffffu] = pa;
@@ -1250,23 +1205,14 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
                 sAcc[t1[r] >> 16] = pc;
                 rUx[r] = Unx;
                 rUy[r] = Uny;
-                if (r < OS && le < h.nown) {
-                    if (first && j == 0)
-                        sm[osl(r)].init(Unx, Uny);
-                    else
-                        sm[osl(r)].add(Unx, Uny);
-                }
+                if (r < OS) sm[osl(r)].add(Unx, Uny);   // (stored for owned triangles alone)
             }
         }
         lds_barrier();
         // vertex phase.  The update of vertex i from its row sum acc (and its elevation,
         // area term and W read beforehand)
         auto finish = [&](int i, T acc, T e_i, T av_i, T w_i) -> T {
-            T en;
-            if constexpr (F32)
-                en = vtx_update_f32(e_i, acc, av_i, w_i, dts);
-            else
-                en = e_i - dts * (acc * av_i + w_i);
+            const T en = vtx_update(e_i, acc, av_i, w_i, dts);
             if constexpr (SM) {
                 const T e1 = sE1[i], e2 = sE2[i];
                 sEA[i] = sesm_am<T>(c, en, e_i, e1, e2);

@@ -279,7 +279,7 @@ __global__ void __launch_bounds__(256) k_zstar_w(TrimArgs a, const double *S) {
 //   2. the trim of each local triangle (TPG per group) into registers, stored to U
 //      when the tile owns the triangle (a triangle of an earlier run's vertex is trimmed
 //      there too, from the same inputs, to the same bits)
-//   3. per block of 8 layers: the trimmed transports to LDS, then each own vertex's
+//   3. per three blocks of 8 layers: the trimmed transports to LDS, then each own vertex's
 //      layer divergences over its row in CSR order
 //   4. w by group suffix sums, bottom up
 // The arithmetic of k_zstar_h + k_trim + k_zstar_w in the same order (the same bits),
@@ -293,6 +293,16 @@ constexpr int TT_VPG = kTrimTileOwn / 32;   // own vertices per group
 // 64-triangle tiles ran 8% faster than 96-triangle ones despite their larger halo)
 template <int L> constexpr int trim_tpg() { return L <= 1 ? 8 : L <= 3 ? 4 : L <= 4 ? 3 : 2; }
 
+// Layer blocks per round of step 3 and the doubles of the vertex columns or a round's
+// transports, whichever are more (the transports lie over the columns, which step 2 has
+// used up).  Three of the five blocks of K = 40 at a time: 4 barriers and 2 readings of
+// every row entry instead of 10 and 5, in less LDS (550k vertices, K = 40: 557 -> 537 us).
+template <int L> constexpr int trim_nb() { return L < 3 ? L : 3; }
+template <int L, int TPG> __host__ __device__ constexpr size_t trim_cols(int cap_v, int K) {
+    const size_t cols = static_cast<size_t>(cap_v) * K, rnd = trim_nb<L>() * 32 * TPG * 16;
+    return ((cols > rnd ? cols : rnd) + 1) & ~static_cast<size_t>(1);
+}
+
 template <int L, int TPG>
 __global__ void __launch_bounds__(256) k_trim_tile(TrimArgs a, const double *S) {
     extern __shared__ __align__(16) double tsm[];
@@ -302,9 +312,10 @@ __global__ void __launch_bounds__(256) k_trim_tile(TrimArgs a, const double *S) 
     const int32_t v0 = hd[0], nvo = hd[1], nvl = hd[2], nel = hd[3], neo = hd[4];
     const int32_t lv_off = hd[5], le_off = hd[6], nent = hd[7];
     constexpr int CE = 32 * TPG;
-    double *sP = tsm;                                                     // [cap_v][K]
-    d2v *sU = reinterpret_cast<d2v *>(tsm + static_cast<size_t>(a.tt_cap_v) * K);   // [CE][8]
-    d2v *sS = sU + CE * 8;                                               // [3 CE]
+    constexpr int NB = trim_nb<L>();
+    double *sP = tsm;                             // [cap_v][K], then, over it,
+    d2v *sU = reinterpret_cast<d2v *>(tsm);       // [NB][CE][8]
+    d2v *sS = reinterpret_cast<d2v *>(tsm + trim_cols<L, TPG>(a.tt_cap_v, K));   // [3 CE]
     uint16_t *sL = reinterpret_cast<uint16_t *>(sS + 3 * CE);             // [3 CE]
     const double inv_tau = 1.0 / a.tau;
     // the loads of steps 2 and 3 that do not wait for LDS, issued first: the local
@@ -408,26 +419,34 @@ __global__ void __launch_bounds__(256) k_trim_tile(TrimArgs a, const double *S) 
             if (own && k < K) st_stream(a.U + 2 * (ge[q] * K + k), r);
         }
     }
-    // 3. layer divergences of the own vertices, one block of 8 layers at a time
+    // 3. layer divergences of the own vertices, NB blocks of 8 layers at a time
     double div[TT_VPG][L];
 #pragma unroll
     for (int q = 0; q < TT_VPG; ++q)
 #pragma unroll
         for (int l = 0; l < L; ++l) div[q][l] = 0.0;
 #pragma unroll
-    for (int l = 0; l < L; ++l) {
+    for (int l0 = 0; l0 < L; l0 += NB) {
+        __syncthreads();   // the columns, or the round before, read by all
 #pragma unroll
         for (int q = 0; q < TPG; ++q)
-            if (grp + 32 * q < nel) sU[(grp + 32 * q) * 8 + g] = Ut[q][l];
+#pragma unroll
+            for (int n = 0; n < NB; ++n)
+                if (l0 + n < L && grp + 32 * q < nel)
+                    sU[(n * CE + grp + 32 * q) * 8 + g] = Ut[q][l0 + n];
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < TT_VPG; ++q)
             for (int jj = j0[q] - jb; jj < j1[q] - jb; ++jj) {
                 const d2v sv = sS[jj];
-                const d2v F = sU[sL[jj] * 8 + g];
-                div[q][l] += F.x * sv.x + F.y * sv.y;
+                const d2v *F = sU + sL[jj] * 8 + g;
+#pragma unroll
+                for (int n = 0; n < NB; ++n)
+                    if (l0 + n < L) {
+                        const d2v f = F[n * CE * 8];
+                        div[q][l0 + n] += f.x * sv.x + f.y * sv.y;
+                    }
             }
-        __syncthreads();
     }
     // 4. w from the bottom up
 #pragma unroll
@@ -635,7 +654,7 @@ int trim_tile_cap_v(int K) { return trim_tile_cap_e(K); }
 template <int L> hipError_t launch_trim_tile_l(const TrimArgs &a, const double *S, hipStream_t s) {
     constexpr int TPG = trim_tpg<L>();
     constexpr int CE = 32 * TPG;
-    const size_t lds = static_cast<size_t>(a.tt_cap_v) * a.K * 8 + CE * (8 * 16 + 3 * 16 + 3 * 2);
+    const size_t lds = trim_cols<L, TPG>(a.tt_cap_v, a.K) * 8 + CE * (3 * 16 + 3 * 2);
     hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(k_trim_tile<L, TPG>),
                                          hipFuncAttributeMaxDynamicSharedMemorySize,
                                          static_cast<int>(lds));

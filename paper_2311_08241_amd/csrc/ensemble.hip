@@ -28,8 +28,8 @@ __global__ void __launch_bounds__(256) k_vol_reduce_batch(const double *part,
     const double *row = part + m.part_off + r * m.width;
     double s = 0.0;
     for (int64_t i = threadIdx.x; i < m.width; i += 256) s += row[i];
-    s = wave_sum(s);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    s = wave_sum_last(s);
+    if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = s;
     __syncthreads();
     if (threadIdx.x == 0) out[m.out_off + r] = m.add + ((red[0] + red[1]) + (red[2] + red[3]));
 }

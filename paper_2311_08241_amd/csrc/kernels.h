@@ -45,6 +45,7 @@ struct TileArgs {
     int32_t se, sv;             // triangle and vertex table entries per tile
     int32_t ell;                // deposits in fixed-width rows (kEllWidth per vertex)
     int32_t early;              // tables loaded before the tile header arrives
+    int32_t direct;             // see eta_u
     int32_t K, chunk;
     int32_t ksub;               // substeps per launch (K; K / 2 with the viscous term)
     const int32_t *lv_gid;
@@ -59,12 +60,15 @@ struct TileArgs {
     const void *lv_av;          // per local vertex: 1 / A_v
     const StepC *mem;           // per-member constants (batches); nullptr: use c0
     StepC c0;
-    void *eta_u, *eta_w;        // ping-pong pair: member chunk ch reads (ch even ? u : w)
+    // ping-pong pair: member chunk ch reads (ch even ? u : w) and writes the other; with
+    // direct every chunk reads u and writes w (the host picks them per launch) and U0c
+    // already holds U^0
+    void *eta_u, *eta_w;
     void *U_u, *U_w;
     const void *R, *f, *H0, *W, *Av;
     const double *Av64;
     void *sum;                  // double2 running sum per triangle (both precisions)
-    void *U0c;                  // copy of U^0
+    void *U0c;                  // U^0 (written by the first chunk unless direct)
     double *Uavg;
     double *vol_part;
     uint32_t *faults;
@@ -74,9 +78,10 @@ struct TileArgs {
     const uint32_t *vnb;
     const void *vgeo;
     double vA0, vCv;
-    // AB3-AM4 only: two sets of (eta, eta^{-1}, eta^{-2}, eta_am) and of
-    // (U, U^{-1}, U_ab), global numbering; chunk ch writes set ch & 1 and reads
-    // set (ch - 1) & 1 (the caller's eta_u / U_u at the member's first chunk)
+    // AB3-AM4 only: (eta, eta^{-1}, eta^{-2}, eta_am) and (U, U^{-1}, U_ab) that the launch
+    // reads ([0]: the caller's state three and two times over at the first) and writes
+    // ([1]), global numbering; picked per launch by the host (an array indexed in the
+    // kernel makes the accesses flat ones)
     void *sm_v[2][4];
     void *sm_e[2][3];
     // forward-backward only (adjoint recompute): when set, the elevation of the owned

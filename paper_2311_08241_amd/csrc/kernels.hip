@@ -704,7 +704,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
     // (0 <= ch, ch KS < nsub), and no early return stands between the first loads
     const int ch = a.chunk - c.chunk0;
     const int m0 = ch * KS;
-    const bool even = (ch & 1) == 0;
+    const bool even = a.direct || (ch & 1) == 0;
     const int cnt = min(KS, c.nsub - m0);
     const int rings = VI ? 2 * cnt : cnt;   // rings this launch needs
     const bool first = m0 == 0, last = m0 + cnt == c.nsub;
@@ -754,22 +754,21 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
     // FP32 vertex gathers go straight to LDS (global_load_lds, the LDS address from
     // M0), FP64 ones through registers.
     constexpr bool dma = F32;
-    // inputs: SE ping-pongs (caller's arrays, workspace); SM reads the caller's
-    // arrays at the member's first chunk, else the set the previous chunk wrote
-    const int rs = (ch - 1) & 1;
+    // inputs: SE ping-pongs (caller's arrays, workspace); SM: set 0 of the launch (the
+    // caller's arrays at the first chunk, else what the previous chunk wrote)
     const bool pend = SM && ch > 0;   // SM: transport update of the previous substep pending
     const T *eta_in = static_cast<const T *>(
-        SM ? (ch == 0 ? a.eta_u : a.sm_v[rs][0]) : (even ? a.eta_u : a.eta_w));
-    const T *e1_in = SM ? static_cast<const T *>(ch == 0 ? a.eta_u : a.sm_v[rs][1]) : nullptr;
-    const T *e2_in = SM ? static_cast<const T *>(ch == 0 ? a.eta_u : a.sm_v[rs][2]) : nullptr;
-    const T *eA_in = SM ? static_cast<const T *>(a.sm_v[rs][3]) : nullptr;
+        SM ? a.sm_v[0][0] : (even ? a.eta_u : a.eta_w));
+    const T *e1_in = SM ? static_cast<const T *>(a.sm_v[0][1]) : nullptr;
+    const T *e2_in = SM ? static_cast<const T *>(a.sm_v[0][2]) : nullptr;
+    const T *eA_in = SM ? static_cast<const T *>(a.sm_v[0][3]) : nullptr;
     const T *H0 = static_cast<const T *>(a.H0);
     const T *Wt = static_cast<const T *>(a.W);
     const T *lav = static_cast<const T *>(a.lv_av) + lv0;   // 1 / A_v
     const T2 *Uin = static_cast<const T2 *>(
-        SM ? (ch == 0 ? a.U_u : a.sm_e[rs][0]) : (even ? a.U_u : a.U_w));
-    const T2 *U1in = SM ? static_cast<const T2 *>(ch == 0 ? a.U_u : a.sm_e[rs][1]) : nullptr;
-    const T2 *UAin = SM ? static_cast<const T2 *>(a.sm_e[rs][2]) : nullptr;
+        SM ? a.sm_e[0][0] : (even ? a.U_u : a.U_w));
+    const T2 *U1in = SM ? static_cast<const T2 *>(a.sm_e[0][1]) : nullptr;
+    const T2 *UAin = SM ? static_cast<const T2 *>(a.sm_e[0][2]) : nullptr;
     const T2 *Rg = static_cast<const T2 *>(a.R);
     const T *fg = static_cast<const T *>(a.f);
     const T dts = cdts<T>(c);
@@ -983,7 +982,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
         const int nz = (kEllWidth * nvu * (int)sizeof(T) + 15) / 16;
         for (int i = tid; i < nz; i += BLOCK) reinterpret_cast<uint4 *>(sAcc)[i] = make_uint4(0, 0, 0, 0);
     }
-    if (first && !SM) {
+    if (first && !SM && !a.direct) {
 #pragma unroll
         for (int r = 0; r < OS; ++r) {
             const int le = tid + r * BLOCK;
@@ -1082,6 +1081,13 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
                 asm volatile("" : "+v"(t0[r]), "+v"(t1[r]), "+v"(t2[r]));
                 asm volatile("" : "+v"(g0[r]), "+v"(g1[r]), "+v"(g2[r]), "+v"(g3[r]), "+v"(g4[r]));
             }
+        }
+        // AB3-AM4 FP32 at four triangles per thread: likewise the packed indices (136 VGPRs
+        // with the deposit and elevation addresses held, one 512-thread tile per CU; 124 and
+        // two: 550k vertices 1395 -> 972 us per 80-substep call)
+        if constexpr (F32 && SM && EPT == 4) {
+#pragma unroll
+            for (int r = 0; r < EPT; ++r) asm volatile("" : "+v"(t0[r]), "+v"(t1[r]), "+v"(t2[r]));
         }
         // FP32 forward-backward: the three elevations of every slot read before any
         // update, so that all slots wait for one LDS round trip
@@ -1315,20 +1321,19 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
 
     // write back owned vertices and triangles
     if constexpr (SM) {
-        const int wsel = ch & 1;
-        T *o0 = static_cast<T *>(a.sm_v[wsel][0]) + h.vbase;
-        T *o1 = static_cast<T *>(a.sm_v[wsel][1]) + h.vbase;
-        T *o2 = static_cast<T *>(a.sm_v[wsel][2]) + h.vbase;
-        T *o3 = static_cast<T *>(a.sm_v[wsel][3]) + h.vbase;
+        T *o0 = static_cast<T *>(a.sm_v[1][0]) + h.vbase;
+        T *o1 = static_cast<T *>(a.sm_v[1][1]) + h.vbase;
+        T *o2 = static_cast<T *>(a.sm_v[1][2]) + h.vbase;
+        T *o3 = static_cast<T *>(a.sm_v[1][3]) + h.vbase;
         for (int i = tid; i < h.nv0; i += BLOCK) {
             st1<nt>(sEta[i], o0 + i);
             st1<nt>(sE1[i], o1 + i);
             st1<nt>(sE2[i], o2 + i);
             st1<nt>(sEA[i], o3 + i);
         }
-        T2 *u0 = static_cast<T2 *>(a.sm_e[wsel][0]);
-        T2 *u1 = static_cast<T2 *>(a.sm_e[wsel][1]);
-        T2 *u2 = static_cast<T2 *>(a.sm_e[wsel][2]);
+        T2 *u0 = static_cast<T2 *>(a.sm_e[1][0]);
+        T2 *u1 = static_cast<T2 *>(a.sm_e[1][1]);
+        T2 *u2 = static_cast<T2 *>(a.sm_e[1][2]);
 #pragma unroll
         for (int r = 0; r < OS; ++r) {   // owned triangles lie in the first OS slots
             const int le = tid + r * BLOCK;
@@ -1358,15 +1363,18 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
             T2 u;
             u.x = rUx[r];
             u.y = rUy[r];
-            st2<nt, T>(Uout, g, u.x, u.y);
-            if (last) {
+            if (!last) {
+                st2<nt, T>(Uout, g, u.x, u.y);
+            } else {
+                // U^0, with a.direct in the array that this store may write
+                T2 u0 = u;
+                if (a.Uavg) u0 = ldp<nt>(static_cast<const T2 *>(a.U0c) + g);
+                st2<nt, T>(Uout, g, u.x, u.y);
                 if (!a.Uavg) continue;
-                const T2 u0 = ldp<nt>(static_cast<const T2 *>(a.U0c) + g);
                 st2<nt, double>(a.Uavg, g, sm[r].vx() / c.Mdbl + c.thM * ((double)u.x - (double)u0.x),
                                sm[r].vy() / c.Mdbl + c.thM * ((double)u.y - (double)u0.y));
-            } else {
-                sm[r].template store<nt>(a.sum, g);
             }
+            if (!last) sm[r].template store<nt>(a.sum, g);
         }
     }
     }
@@ -1925,8 +1933,8 @@ __global__ void __launch_bounds__(256) k_vol_reduce(const double *part, int64_t 
     const int r = blockIdx.x;
     double s = 0.0;
     for (int64_t i = threadIdx.x; i < width; i += 256) s += part[r * width + i];
-    s = wave_sum(s);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    s = wave_sum_last(s);
+    if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = s;
     __syncthreads();
     if (threadIdx.x == 0) out[r] = add + ((red[0] + red[1]) + (red[2] + red[3]));
 }

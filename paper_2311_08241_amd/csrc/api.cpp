@@ -1554,7 +1554,7 @@ se_status se_subcycle_adjoint(se_mesh *m, const se_params *p, const void *eta0, 
         ra.cs_row = P.cs_row.as<const uint16_t>();
         ra.lgeo = f32 ? P.geo32.p : P.geo64.p;
         ra.lae = f32 ? P.ae32.p : P.ae64.p;
-        ra.Av = fa.Av;
+        ra.lv_av = f32 ? P.lav32.p : P.lav64.p;
         ra.H0 = fo->H0;
         ra.f = fo->f;
         ra.traj_stride = nv;

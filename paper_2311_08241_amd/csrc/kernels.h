@@ -27,6 +27,9 @@ enum : int32_t { KF_LINEAR_H = 1, KF_TRACK_VOLUME = 4 };
 // distinct LDS banks).
 constexpr int kEllWidth = 7;
 
+// Most rings (inner substeps) of one launch.
+constexpr int kMaxFused = 8;
+
 // Triangle slots per thread that can hold owned triangles (the first ones of the
 // local order), for EPT slots in all: only these carry running-sum registers.
 __host__ __device__ constexpr int own_slots(int ept) { return ept <= 2 ? ept : ept - 1; }
@@ -106,7 +109,8 @@ struct AdjTileArgs {
     int32_t se, sv;             // triangle and vertex table entries per tile
     const uint16_t *cs_row;
     const void *lgeo, *lae;     // per local triangle: gbx gby gcx gcy; A_e
-    const void *Av, *H0, *f;    // global numbering, the precision's type
+    const void *lv_av;          // per local vertex: 1 / A_v
+    const void *H0, *f;         // global numbering, the precision's type
     // forward elevation of slot s: s == 0 ? eta_s0 : traj + s * traj_stride
     const void *eta_s0, *traj;
     int64_t traj_stride;

@@ -1688,6 +1688,11 @@ __device__ __forceinline__ void adj_tile_body(const AdjTileArgs &a, int b, int G
     for (int k = 0; k < NVO; ++k) gh[k] = a.seed ? T(0) : gHg[h.vbase + min(tid + k * BLOCK, h.nv0 - 1)];
     const uint2 *crow = reinterpret_cast<const uint2 *>(a.cs_row + h.rw_off);
     const int nrow4 = a.ell ? 0 : (nvu + 1 + 3) >> 2;
+    // vertex slots per thread staged in the rounds (as in the forward tile kernel)
+    constexpr int VS = EPT / 2 + 1;
+    int gv[VS];
+#pragma unroll
+    for (int u = 0; u < VS; ++u) gv[u] = lv[min(max(tid + u * BLOCK, h.nv0), nv_load - 1)];
     const int lev_cnt = tid <= K ? nV[tid] : 0;
     const int lev_cnt_e = tid <= K ? nE[tid] : 0;
     __builtin_amdgcn_s_waitcnt(0);   // round A complete
@@ -1700,18 +1705,28 @@ __device__ __forceinline__ void adj_tile_body(const AdjTileArgs &a, int b, int G
 
     const T *lein = static_cast<const T *>(a.lam_eta_in);
     const T *H0g = static_cast<const T *>(a.H0);
-    const T *Avg = static_cast<const T *>(a.Av);
-    for (int i = tid; i < nv_load; i += BLOCK) {
-        const int g = ldp<nt>(lv + i);
-        sLe[i] = lein ? lein[g] : T(0);   // null only for a zero seed
-        sH[i] = H0g[g];
-        sAv[i] = T(1) / Avg[g];   // reciprocal area
-        for (int j = 0; j < cnt; ++j) {
-            const int sl = a.s_hi - 1 - j;
-            const T *es = sl == 0 ? static_cast<const T *>(a.eta_s0)
-                                  : static_cast<const T *>(a.traj) + (int64_t)sl * a.traj_stride;
-            sEm[j * a.cap_nv + i] = es[g];
-        }
+    const T *lav = static_cast<const T *>(a.lv_av) + static_cast<int64_t>(b) * a.sv;   // 1 / A_v
+    // forward elevation of inner step j: slot sl of the trajectory, slot 0 the checkpoint
+    auto em_of = [&](int j) -> const T * {
+        const int sl = a.s_hi - 1 - j;
+        return sl == 0 ? static_cast<const T *>(a.eta_s0)
+                       : static_cast<const T *>(a.traj) + (int64_t)sl * a.traj_stride;
+    };
+    // every load of a slot (and of all slots, as registers allow) issued before any is
+    // stored: one after the other, the cnt elevations of a vertex cost a memory round trip
+    // each (65,536 vertices FP64, forward and 30-substep adjoint: 465 -> 447 us)
+    T vle[VS], vh[VS], va[VS], vem[VS][kMaxFused];
+#pragma unroll
+    for (int u = 0; u < VS; ++u) {
+        if (u > 0 && u * BLOCK >= nv_load) continue;
+        const int i = min(tid + u * BLOCK, nv_load - 1);
+        const int g = i < h.nv0 ? h.vbase + i : gv[u];
+        vle[u] = lein ? lein[g] : T(0);   // null only for a zero seed
+        vh[u] = H0g[g];
+        va[u] = lav[i];
+#pragma unroll
+        for (int j = 0; j < kMaxFused; ++j)
+            if (j < cnt) vem[u][j] = em_of(j)[g];
     }
     const T dts = cdts<T>(c);
     if (ne_load > 0) {
@@ -1743,6 +1758,24 @@ __device__ __forceinline__ void adj_tile_body(const AdjTileArgs &a, int b, int G
                 suy[r] = T(0);
             }
         }
+    }
+#pragma unroll
+    for (int u = 0; u < VS; ++u) {
+        const int i = tid + u * BLOCK;
+        if (i >= nv_load) continue;
+        sLe[i] = vle[u];
+        sH[i] = vh[u];
+        sAv[i] = va[u];
+#pragma unroll
+        for (int j = 0; j < kMaxFused; ++j)
+            if (j < cnt) sEm[j * a.cap_nv + i] = vem[u][j];
+    }
+    for (int i = tid + VS * BLOCK; i < nv_load; i += BLOCK) {
+        const int g = lv[i];
+        sLe[i] = lein ? lein[g] : T(0);
+        sH[i] = H0g[g];
+        sAv[i] = lav[i];
+        for (int j = 0; j < cnt; ++j) sEm[j * a.cap_nv + i] = em_of(j)[g];
     }
     for (int i = tid; i < nrow4; i += BLOCK) reinterpret_cast<uint2 *>(sRow)[i] = ldp<nt>(crow + i);
     if (tid <= K) {

@@ -144,7 +144,15 @@ se_status plan_host(const std::vector<const HostMesh *> &members, const std::vec
             if (over > 0 && over * 50 <= nt) {
                 HostTiles hs;
                 SE_TRY(build_tiles(members, voff, eoff, T, K, hs, cap));
-                if (hs.max_ne <= cap) ht = std::move(hs);
+                // the workspace holds volume partials of one tile per 64 vertices of a member
+                // (whatever the plan): halves beyond that, which tiles near 64 vertices
+                // can give, would write past it
+                std::vector<int64_t> cnt(members.size(), 0);
+                for (const TileHdr &h : hs.hdr) ++cnt[h.member];
+                bool fits = hs.max_ne <= cap;
+                for (size_t i = 0; i < members.size(); ++i)
+                    fits = fits && cnt[i] <= (members[i]->nv + 63) / 64;
+                if (fits) ht = std::move(hs);
             }
         }
     }

@@ -205,6 +205,16 @@ def test_plan_halves_the_few_tiles_above_the_next_lower_tier():
     assert st["ntiles"] == -(-nv // 576)
 
 
+@pytest.mark.parametrize("k_fused, block", [(4, 512), (7, 256), (7, 512), (7, 1024)])
+def test_plan_never_holds_more_tiles_than_the_workspace_has_volume_partials_for(k_fused, block):
+    """The workspace keeps one volume partial per 64 vertices and substep for any plan; the
+    halving of oversized 64-vertex tiles along a coast must not go beyond (the mesh keeps
+    uniform tiles then)."""
+    mesh = Mesh.from_dict(sesynth.latlon_c3(nlon=300, nlat=211), device=-1)
+    st = mesh.plan_stats(64, k_fused, block)
+    assert st["ntiles"] <= (mesh.nv + 63) // 64
+
+
 def test_autotune_candidates_and_signature_on_a_host_mesh():
     """The tuner's host side: plan ranking for both schemes and the cache key."""
     from paper_2311_08241_amd import Mesh

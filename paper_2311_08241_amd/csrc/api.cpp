@@ -4,6 +4,7 @@
 #include <cmath>
 #include <complex>
 #include <cstring>
+#include <initializer_list>
 #include <string>
 
 #include "consumers.h"
@@ -200,13 +201,10 @@ se_status plan_host(const std::vector<const HostMesh *> &members, const std::vec
     return SE_OK;
 }
 
-// Build and upload a tile plan for a set of meshes forming a disjoint union.
-se_status make_plan(const std::vector<const HostMesh *> &members, const std::vector<int64_t> &voff,
-                    const std::vector<int64_t> &eoff, int32_t T, int32_t K, int32_t block,
-                    std::unique_ptr<DevTiles> &out) {
-    HostTiles ht;
-    se_plan_stats_t st;
-    SE_TRY(plan_host(members, voff, eoff, T, K, block, ht, st));
+// Upload a tile plan built by plan_host (ht is used up).
+se_status upload_plan(const std::vector<const HostMesh *> &members, const std::vector<int64_t> &voff,
+                      const std::vector<int64_t> &eoff, int32_t T, int32_t K, int32_t block,
+                      HostTiles &ht, const se_plan_stats_t &st, std::unique_ptr<DevTiles> &out) {
     const int ept = st.tri_per_thread;
     if (!st.ok_f32 && !st.ok_f64) {
         set_error("se_set_plan: tile too large for the register or LDS budget (reduce tile or "
@@ -332,6 +330,28 @@ se_status make_plan(const std::vector<const HostMesh *> &members, const std::vec
     }
     out = std::move(p);
     return SE_OK;
+}
+
+// Build and upload a tile plan for a set of meshes forming a disjoint union.
+se_status make_plan(const std::vector<const HostMesh *> &members, const std::vector<int64_t> &voff,
+                    const std::vector<int64_t> &eoff, int32_t T, int32_t K, int32_t block,
+                    std::unique_ptr<DevTiles> &out) {
+    HostTiles ht;
+    se_plan_stats_t st;
+    SE_TRY(plan_host(members, voff, eoff, T, K, block, ht, st));
+    return upload_plan(members, voff, eoff, T, K, block, ht, st, out);
+}
+
+// LDS of the viscous form of a plan whose forward-backward form takes lds bytes: the
+// velocities u = U / H_e of the tile's triangles and their edge-neighbour ids besides.
+size_t visc_lds(size_t lds, bool f32, int32_t max_ne) {
+    const size_t n = static_cast<size_t>(max_ne);
+    return ((lds + 2 * (f32 ? 4 : 8) * n + 15) & ~static_cast<size_t>(15)) + 8 * n;
+}
+// Register budget of the viscous form (no spills): 1024-thread workgroups up to three
+// triangles per thread (FP32; FP64 one), 512-thread ones up to six (FP32) or four (FP64).
+bool visc_regs_ok(bool f32, int block, int ept) {
+    return block == 1024 ? ept <= (f32 ? 3 : 1) : block == 512 ? ept <= (f32 ? 6 : 4) : true;
 }
 
 struct Layout {
@@ -579,26 +599,182 @@ se_status check_device(const se_mesh *m) {
     return SE_OK;
 }
 
-// Default plan when the caller set none: the first candidate that runs in
-// both precisions without spills.
-se_status ensure_plan(se_mesh *m) {
-    if (m->plan) return SE_OK;
-    std::vector<const HostMesh *> mem{&m->h};
-    static const int32_t cand[][3] = {{1024, 4, 512}, {512, 4, 512}, {512, 4, 256}, {512, 2, 256},
-                                      {256, 4, 256}, {256, 2, 256}, {128, 2, 256}, {64, 1, 256}};
+// Forms of the subcycle that a default plan is chosen for.
+enum : int { CL_FB = 0, CL_SESM = 2, CL_VISC = 4, CL_ANY = 6 };   // + 1: FP32; ANY: every form
+
+bool plan_fits(int cl, const HostTiles &ht, const se_plan_stats_t &st, int32_t K, int32_t block) {
+    const bool f32 = cl & 1;
+    switch (cl & ~1) {
+        case CL_FB: return f32 ? st.ok_f32 : st.ok_f64;
+        case CL_SESM: return f32 ? st.ok_sesm_f32 : st.ok_sesm_f64;
+        case CL_VISC:
+            return (f32 ? st.ok_f32 : st.ok_f64) && K >= 2 &&
+                   visc_lds(f32 ? st.lds_f32 : st.lds_f64, f32, ht.max_ne) <= 160 * 1024 &&
+                   visc_regs_ok(f32, block, st.tri_per_thread);
+        default: return st.ok_f32 && st.ok_f64 && st.ok_sesm_f32 && st.ok_sesm_f64;
+    }
+}
+
+// A candidate of a form's default plan: at most ept triangles per thread, and ntiles
+// tiles (0: any number).
+struct PlanCand {
+    int32_t T, K, block, ept, ntiles;
+};
+
+// Candidates of a form's default plan, best first, from the mesh size alone.
+//
+// A launch costs its dependent round trips and its substeps' barriers whatever the tile
+// holds, so a mesh of up to about 200,000 vertices runs fastest as one tile per CU (256 of
+// them, or tiles of 64 vertices where that leaves CUs idle), with as many rings as the
+// register tier takes: fewer launches beat the larger halo.  Two 512-thread workgroups on
+// a CU hold what one of 1024 threads does; the larger one has less halo and, alone, loads
+// faster.  Beyond, FP64 keeps 1024-thread tiles of at most 776 vertices in whole rounds of
+// 256, and FP32 from about 400,000 vertices (both precisions from 700,000) the two-per-CU
+// tiles whose loads overlap the other's substeps.  Each line is the fastest, or within 3%
+// of it, of 20 to 130 plans timed per size (60 substeps, us; vertices: FP32, FP64):
+//   forward-backward  2,048: 90, 91   31,439: 110, 119   69,721: 123, 141
+//                     131,230: 158, 229   195,440: 214, 307   358,386: 381, 539
+//                     550,482: 525, 852   979,989: 869, 1448
+//   AB3-AM4           11,397: 116, 129   195,440: 275, 511   550,482: 674, 1512
+//   viscous           11,397: 210, 241   195,440: 595, 1108   550,482: 1577, 3074
+// One list for every mesh and form (512,4,512 on most) took e.g. 145 FP64 at 11,397
+// vertices and 37 substeps (81 now), 1,140 viscous FP32 at 196,608 (611).
+std::vector<PlanCand> default_plans(int cl, int64_t nv) {
+    std::vector<PlanCand> c;
+    // tiles of at most tmax vertices in whole rounds of 256, a little larger where the
+    // halving of oversized tiles adds some beyond; rings ks, largest first
+    auto rounds = [&](int32_t tmax, std::initializer_list<int32_t> ks, int32_t block, int32_t ept) {
+        const int64_t m = std::max<int64_t>(1, (nv + 256 * static_cast<int64_t>(tmax) - 1) /
+                                                   (256 * static_cast<int64_t>(tmax)));
+        const int32_t T = static_cast<int32_t>(((nv + 256 * m - 1) / (256 * m) + 7) / 8 * 8);
+        for (int32_t K : ks)
+            for (int32_t d = 0; d <= 16; d += 8)
+                c.push_back({std::max<int32_t>(64, T) + d, K, block, ept,
+                             static_cast<int32_t>(256 * m)});
+    };
+    const bool tiny = nv <= 64 * 256;
+    switch (cl) {
+        case CL_FB + 1:
+            if (tiny) c.push_back({64, 8, 512, 4, 0});
+            else if (nv <= 288 * 256) rounds(288, {8, 6, 5}, 512, 4);
+            if (nv <= 1024 * 256) rounds(1024, {8, 6, 5}, 1024, 4);
+            else if (nv <= 400000) rounds(784, {8, 6, 5}, 1024, 4);
+            if (nv <= 700000) c.push_back({384, 5, 512, 4, 0});
+            c.push_back({512, 4, 512, 4, 0});
+            c.push_back({448, 4, 512, 4, 0});
+            break;
+        case CL_FB:
+            if (tiny) c.push_back({64, 6, 1024, 1, 0});
+            if (nv <= 320 * 256) rounds(320, {8}, 1024, 2);
+            if (nv <= 700000) rounds(776, {6, 5, 4}, 1024, 3);
+            c.push_back({320, 4, 512, 3, 0});
+            c.push_back({256, 4, 512, 3, 0});
+            break;
+        case CL_SESM + 1:
+            if (tiny) c.push_back({64, 8, 512, 4, 0});
+            else if (nv <= 800 * 256) rounds(800, {8, 6, 5}, 1024, 3);
+            c.push_back({384, 5, 512, 4, 0});
+            c.push_back({384, 4, 512, 4, 0});
+            break;
+        case CL_SESM:
+            if (tiny) c.push_back({64, 8, 512, 4, 0});
+            else if (nv <= 400000) rounds(392, {6, 5, 4}, 512, 4);
+            c.push_back({384, 5, 512, 4, 0});
+            c.push_back({384, 4, 512, 4, 0});
+            break;
+        case CL_VISC + 1:
+            if (tiny) c.push_back({64, 8, 1024, 3, 0});
+            else if (nv <= 700000) rounds(800, {8, 6, 4}, 1024, 3);
+            c.push_back({352, 4, 512, 3, 0});
+            c.push_back({320, 4, 512, 3, 0});
+            break;
+        case CL_VISC:
+            if (tiny) c.push_back({64, 6, 1024, 1, 0});
+            else if (nv <= 200 * 256) rounds(200, {4}, 1024, 1);
+            if (nv <= 400000) rounds(392, {6, 4}, 512, 4);
+            c.push_back({448, 4, 512, 4, 0});
+            c.push_back({384, 4, 512, 4, 0});
+            break;
+        default: break;
+    }
+    return c;
+}
+
+// Plans that run every form without spills, largest tiles first: the default before a
+// form's own, and the one that a call that may not allocate falls back on.
+const std::vector<PlanCand> kAnyPlans = {
+    {1024, 4, 512, 8, 0}, {512, 4, 512, 8, 0}, {512, 4, 256, 8, 0}, {512, 2, 256, 8, 0},
+    {256, 4, 256, 8, 0},  {256, 2, 256, 8, 0}, {128, 2, 256, 8, 0}, {64, 1, 256, 8, 0}};
+
+// Build the first candidate that fits the form on this mesh.
+se_status make_default(se_mesh *m, int cl, const std::vector<PlanCand> &cand,
+                       std::unique_ptr<DevTiles> &out, bool *any_ok) {
+    const std::vector<const HostMesh *> mem{&m->h};
+    const std::vector<int64_t> vo{0, m->h.nv}, eo{0, m->h.ne};
     for (const auto &c : cand) {
         HostTiles ht;
         se_plan_stats_t st;
-        if (plan_host(mem, {0, m->h.nv}, {0, m->h.ne}, c[0], c[1], c[2], ht, st) != SE_OK) continue;
-        if (!st.ok_f32 || !st.ok_f64 || !st.ok_sesm_f32 || !st.ok_sesm_f64) continue;
-        SE_TRY(make_plan(mem, {0, m->h.nv}, {0, m->h.ne}, c[0], c[1], c[2], m->plan));
-        m->plan_T = c[0];
-        m->plan_K = c[1];
-        m->plan_block = c[2];
-        return SE_OK;
+        // not worth building: the local triangles of a square tile and its rings, less the
+        // tenth that a coast or the edge of the mesh takes off
+        const double side = std::sqrt(static_cast<double>(c.T)) + 2.0 * c.K;
+        if (c.T < m->h.nv && 0.9 * 2.0 * side * side > static_cast<double>(c.ept) * c.block) continue;
+        if (plan_host(mem, vo, eo, c.T, c.K, c.block, ht, st) != SE_OK) continue;
+        if (st.tri_per_thread < 1 || st.tri_per_thread > c.ept || (c.ntiles && st.ntiles > c.ntiles) ||
+            !plan_fits(cl, ht, st, c.K, c.block))
+            continue;
+        if (any_ok) *any_ok = plan_fits(CL_ANY, ht, st, c.K, c.block);
+        return upload_plan(mem, vo, eo, c.T, c.K, c.block, ht, st, out);
     }
     set_error("no default plan fits this mesh");
     return SE_ERR_ARG;
+}
+
+// The plan a call of form cl runs on: the caller's (se_set_plan), else the form's default,
+// made at its first call, else (nothing may be allocated: se_subcycle_noalloc, or a stream
+// under capture once some default exists) one that runs every form.  The first default of
+// a mesh brings such a plan along, so a call that found a plan before still finds one.
+// Results do not depend on the plan.
+se_status mesh_plan(se_mesh *m, int cl, bool may_alloc, hipStream_t s, DevTiles **out) {
+    *out = nullptr;
+    if (m->plan) {
+        *out = m->plan.get();
+        return SE_OK;
+    }
+    std::lock_guard<std::mutex> lk(m->plan_mu);
+    if (m->dflt[cl]) {
+        *out = m->dflt[cl].get();
+        return SE_OK;
+    }
+    DevTiles *any = m->dflt[CL_ANY].get();
+    if (any && may_alloc && s) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)
+            may_alloc = false;
+    }
+    if (!may_alloc) {
+        *out = any;   // null: no plan yet
+        return SE_OK;
+    }
+    std::unique_ptr<DevTiles> p;
+    bool any_ok = false;
+    auto cand = default_plans(cl, m->h.nv);
+    cand.insert(cand.end(), kAnyPlans.begin(), kAnyPlans.end());
+    SE_TRY(make_default(m, cl, cand, p, &any_ok));
+    if (!any) {
+        // a form whose own plan runs every form needs no second one
+        if (!any_ok) {
+            std::unique_ptr<DevTiles> a;
+            SE_TRY(make_default(m, CL_ANY, kAnyPlans, a, nullptr));
+            m->dflt[CL_ANY] = std::move(a);
+        }
+        m->plan_T = p->T;
+        m->plan_K = p->K;
+        m->plan_block = p->block;
+    }
+    m->dflt[cl] = std::move(p);
+    if (!m->dflt[CL_ANY]) m->dflt[CL_ANY] = m->dflt[cl];
+    *out = m->dflt[cl].get();
+    return SE_OK;
 }
 
 }  // namespace
@@ -607,7 +783,7 @@ se_status ensure_plan(se_mesh *m) {
 using namespace sesub;
 
 static se_status ensure_visc(se_mesh *m);
-static se_status ensure_tile_visc(se_mesh *m);
+static se_status ensure_tile_visc(const se_mesh *m, DevTiles &P);
 static ViscArgs visc_args(const se_mesh *m, bool f32, const se_params *p, const void *H0,
                           const void *eta, const void *U, void *ubar);
 
@@ -769,6 +945,10 @@ se_status se_set_plan(void *obj, int32_t kind, int32_t tile, int32_t k_fused, in
     std::unique_ptr<DevTiles> p;
     std::vector<const HostMesh *> mem{&m->h};
     SE_TRY(make_plan(mem, {0, m->h.nv}, {0, m->h.ne}, tile, k_fused, block, p));
+    {
+        std::lock_guard<std::mutex> lk(m->plan_mu);
+        for (auto &d : m->dflt) d.reset();
+    }
     m->plan = std::move(p);
     m->plan_T = tile;
     m->plan_K = k_fused;
@@ -914,16 +1094,17 @@ se_status sesub::subcycle_tile(se_mesh *m, const se_params *p, se_state *st,
     SE_TRY(check_state(st, fo, ws));
     SE_TRY(check_device(m));
     DeviceGuard dg(m->device);
-    if (may_alloc) {
-        SE_TRY(ensure_plan(m));
-    } else if (!m->plan) {
+    const bool f32 = p->precision == SE_F32_MIXED;
+    const bool sm = p->scheme == SE_SCHEME_SESM;
+    DevTiles *PP = nullptr;
+    SE_TRY(mesh_plan(m, (visc ? CL_VISC : sm ? CL_SESM : CL_FB) + (f32 ? 1 : 0), may_alloc,
+                     static_cast<hipStream_t>(stream), &PP));
+    if (!PP) {
         set_error("se_subcycle_noalloc: the mesh has no tile plan yet (se_set_plan, or one "
                   "se_subcycle call, makes one)");
         return SE_ERR_ARG;
     }
-    const DevTiles &P = *m->plan;
-    const bool f32 = p->precision == SE_F32_MIXED;
-    const bool sm = p->scheme == SE_SCHEME_SESM;
+    DevTiles &P = *PP;
     if (!P.ok(f32, sm)) {
         set_error("se_subcycle: the current plan does not fit the register/LDS budget of this "
                   "precision and scheme (see se_plan_stats)");
@@ -932,15 +1113,9 @@ se_status sesub::subcycle_tile(se_mesh *m, const se_params *p, se_state *st,
     const size_t es = f32 ? 4 : 8;
     size_t lds = P.lds(f32, sm);
     if (visc) {
-        // two rings per substep; the velocities u = U / H_e of the tile's triangles and
-        // their edge-neighbour ids in LDS
-        lds = ((lds + 2 * es * static_cast<size_t>(P.max_ne) + 15) & ~static_cast<size_t>(15)) +
-              8 * static_cast<size_t>(P.max_ne);
-        // register budget of the viscous form (no spills): 1024-thread workgroups up to
-        // three triangles per thread (FP32; FP64 one), 512-thread ones up to six (FP32)
-        // or four (FP64)
-        const bool regs_ok = P.block == 1024 ? P.ept <= (f32 ? 3 : 1)
-                             : P.block == 512 ? P.ept <= (f32 ? 6 : 4) : true;
+        // two rings per substep
+        lds = visc_lds(lds, f32, P.max_ne);
+        const bool regs_ok = visc_regs_ok(f32, P.block, P.ept);
         if (P.K < 2 || lds > 160 * 1024 || !regs_ok) {
             set_error("se_subcycle: with the viscous term the plan needs k_fused >= 2, " +
                       std::to_string(lds) + " bytes of LDS within 160 KiB and at most " +
@@ -948,13 +1123,13 @@ se_status sesub::subcycle_tile(se_mesh *m, const se_params *p, se_state *st,
                       "(FP32 / FP64)");
             return SE_ERR_ARG;
         }
-        if (!may_alloc && (!m->d.vnb.p || !m->plan->vnb.p)) {
+        if (!may_alloc && (!m->d.vnb.p || !P.vnb.p)) {
             set_error("se_subcycle_noalloc: the viscous tables of this mesh and plan are not "
                       "built yet (one se_subcycle call with the viscous term builds them)");
             return SE_ERR_ARG;
         }
         SE_TRY(ensure_visc(m));
-        SE_TRY(ensure_tile_visc(m));
+        SE_TRY(ensure_tile_visc(m, P));
     }
     const hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t nv = m->h.nv, ne = m->h.ne;
@@ -1240,8 +1415,7 @@ static se_status ensure_visc(se_mesh *m) {
 // every local triangle, the local index of the triangle across each edge when it
 // belongs to the tile (0xffff otherwise: a coast, or a neighbour beyond the loaded
 // rings, which no updated triangle uses), and the edge geometry.
-static se_status ensure_tile_visc(se_mesh *m) {
-    DevTiles &P = *m->plan;
+static se_status ensure_tile_visc(const se_mesh *m, DevTiles &P) {
     if (P.vnb.p) return SE_OK;
     std::vector<int32_t> nb4;
     std::vector<double> vg;
@@ -1470,7 +1644,14 @@ se_status se_subcycle_adjoint(se_mesh *m, const se_params *p, const void *eta0, 
     auto seg_U = [&](int32_t sg, int32_t j) -> const void * {
         return j == 0 ? ckpt_U(sg) : st_U(seg_off(sg, j));
     };
+    // the caller's plan, or a default that the forward subcycle made: the form's own where
+    // it runs the reverse kernel, else the one for every form
     const DevTiles *TP = m->plan.get();
+    if (!TP) {
+        std::lock_guard<std::mutex> lk(m->plan_mu);
+        TP = m->dflt[CL_FB + (f32 ? 1 : 0)].get();
+        if (!TP || !TP->adj_ready[f32 ? 1 : 0]) TP = m->dflt[CL_ANY].get();
+    }
     if (TP && TP->ok(f32, false) && TP->prepared[f32 ? 1 : 0]) {
         // The mesh has a tile plan for this precision: each segment runs as temporally
         // blocked launches from checkpoint q to checkpoint q + 1 (the tile path equals

@@ -6,6 +6,7 @@
 #include <cstdint>
 #include <map>
 #include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -175,6 +176,11 @@ struct se_mesh {
     int device = 0;
     sesub::HostMesh h;
     sesub::DevMesh d;
-    std::unique_ptr<sesub::DevTiles> plan;
+    std::unique_ptr<sesub::DevTiles> plan;      // the caller's (se_set_plan)
+    // defaults made on first use while the caller has set none: per form of the subcycle
+    // (forward-backward, AB3-AM4, viscous; FP64, FP32), and one that runs every form
+    // (one of the others where that runs them all)
+    std::shared_ptr<sesub::DevTiles> dflt[7];
+    std::mutex plan_mu;                         // guards dflt
     int32_t plan_T = 1024, plan_K = 4, plan_block = 256;
 };

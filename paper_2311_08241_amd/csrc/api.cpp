@@ -1931,17 +1931,38 @@ se_status batch_install_plan(se_batch *b, int32_t T, int32_t K, int32_t block) {
     return SE_OK;
 }
 
-se_status batch_ensure_plan(se_batch *b) {
+// Default plan of a batch, chosen at its first call from the vertices of all members and
+// the call's precision, among the plans that run in both: about one 512-thread tile per CU
+// with many rings while the members together are that small, else two per CU.  24 basins
+// of 3,000 to 40,000 vertices (513,187 in all) FP32: 512,2,512 1045, 352,5,512 722 us per
+// call cold; FP64 1927, 256,4,512 1234; eight of 2,000 to 8,000 (36,883) 256,4,512 236 and
+// 283, 128,8,512 196 and 233.
+se_status batch_ensure_plan(se_batch *b, bool f32) {
     if (b->plan) return SE_OK;
-    static const int32_t cand[][3] = {{768, 4, 512}, {512, 4, 512}, {512, 2, 512}, {256, 4, 512},
-                                      {256, 2, 256}, {128, 2, 256}, {64, 1, 256}};
+    std::vector<PlanCand> cand;
+    if (b->nv <= 75000) {
+        const int32_t T = std::max<int32_t>(64, static_cast<int32_t>((b->nv + 287) / 288 + 7) / 8 * 8);
+        for (int32_t K : {8, 6, 5}) cand.push_back({T, K, 512, 4, 0});
+    }
+    if (f32) {
+        cand.push_back({352, 5, 512, 4, 0});
+        cand.push_back({320, 5, 512, 4, 0});
+        cand.push_back({448, 4, 512, 4, 0});
+    }
+    cand.push_back({256, 4, 512, 3, 0});
+    cand.push_back({256, 4, 512, 4, 0});
+    for (const PlanCand &c : {PlanCand{768, 4, 512, 8, 0}, PlanCand{512, 4, 512, 8, 0},
+                              PlanCand{512, 2, 512, 8, 0}, PlanCand{256, 4, 512, 8, 0},
+                              PlanCand{256, 2, 256, 8, 0}, PlanCand{128, 2, 256, 8, 0},
+                              PlanCand{64, 1, 256, 8, 0}})
+        cand.push_back(c);
     for (const auto &c : cand) {
         HostTiles ht;
         se_plan_stats_t st;
-        if (plan_host(batch_members(b), b->voff, b->eoff, c[0], c[1], c[2], ht, st) != SE_OK)
+        if (plan_host(batch_members(b), b->voff, b->eoff, c.T, c.K, c.block, ht, st) != SE_OK)
             continue;
-        if (!st.ok_f32 || !st.ok_f64 || !st.ok_sesm_f32 || !st.ok_sesm_f64) continue;
-        return batch_install_plan(b, c[0], c[1], c[2]);
+        if (!st.ok_f32 || !st.ok_f64 || st.tri_per_thread > c.ept) continue;
+        return batch_install_plan(b, c.T, c.K, c.block);
     }
     set_error("no default plan fits this batch");
     return SE_ERR_ARG;
@@ -2095,7 +2116,7 @@ se_status se_subcycle_batched(se_batch *b, const se_params *p, se_state *st, con
         return SE_ERR_ARG;
     }
     DeviceGuard dg(b->device);
-    SE_TRY(batch_ensure_plan(b));
+    SE_TRY(batch_ensure_plan(b, p->precision == SE_F32_MIXED));
     const DevTiles &P = *b->plan;
     const bool f32 = p->precision == SE_F32_MIXED;
     if (!(f32 ? P.ok32 : P.ok64)) {

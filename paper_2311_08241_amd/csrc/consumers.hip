@@ -279,7 +279,7 @@ __global__ void __launch_bounds__(256) k_zstar_w(TrimArgs a, const double *S) {
 //   2. the trim of each local triangle (TPG per group) into registers, stored to U
 //      when the tile owns the triangle (a triangle of an earlier run's vertex is trimmed
 //      there too, from the same inputs, to the same bits)
-//   3. per three blocks of 8 layers: the trimmed transports to LDS, then each own vertex's
+//   3. per round of up to four blocks of 8 layers: the trimmed transports to LDS, then each own vertex's
 //      layer divergences over its row in CSR order
 //   4. w by group suffix sums, bottom up
 // The arithmetic of k_zstar_h + k_trim + k_zstar_w in the same order (the same bits),
@@ -295,9 +295,17 @@ template <int L> constexpr int trim_tpg() { return L <= 1 ? 8 : L <= 3 ? 4 : L <
 
 // Layer blocks per round of step 3 and the doubles of the vertex columns or a round's
 // transports, whichever are more (the transports lie over the columns, which step 2 has
-// used up).  Three of the five blocks of K = 40 at a time: 4 barriers and 2 readings of
-// every row entry instead of 10 and 5, in less LDS (550k vertices, K = 40: 557 -> 537 us).
-template <int L> constexpr int trim_nb() { return L < 3 ? L : 3; }
+// used up): as few rounds as leave room for four workgroups per CU (40 KB of LDS each), of
+// even sizes.  K = 40 takes its five blocks as three and two: 4 barriers and 2 readings of
+// every row entry instead of 10 and 5, in less LDS (550k vertices: 557 -> 537 us).  Three
+// blocks of 128-triangle tiles would leave two workgroups per CU (K = 24, 550k vertices:
+// 336 us; 465 with three, 390 with one block per round).
+template <int L> constexpr int trim_nb() {
+    constexpr int CE = 32 * trim_tpg<L>();
+    constexpr int fit = (40 * 1024 - CE * 54) / (CE * 128), most = fit < 1 ? 1 : fit < L ? fit : L;
+    constexpr int rounds = (L + most - 1) / most;
+    return (L + rounds - 1) / rounds;
+}
 template <int L, int TPG> __host__ __device__ constexpr size_t trim_cols(int cap_v, int K) {
     const size_t cols = static_cast<size_t>(cap_v) * K, rnd = trim_nb<L>() * 32 * TPG * 16;
     return ((cols > rnd ? cols : rnd) + 1) & ~static_cast<size_t>(1);

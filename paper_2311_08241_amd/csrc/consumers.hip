@@ -279,8 +279,8 @@ __global__ void __launch_bounds__(256) k_zstar_w(TrimArgs a, const double *S) {
 //   2. the trim of each local triangle (TPG per group) into registers, stored to U
 //      when the tile owns the triangle (a triangle of an earlier run's vertex is trimmed
 //      there too, from the same inputs, to the same bits)
-//   3. per round of up to four blocks of 8 layers: the trimmed transports to LDS, then each own vertex's
-//      layer divergences over its row in CSR order
+//   3. per round of up to four blocks of 8 layers: the trimmed transports to LDS, then each
+//      own vertex's layer divergences over its row in CSR order
 //   4. w by group suffix sums, bottom up
 // The arithmetic of k_zstar_h + k_trim + k_zstar_w in the same order (the same bits),
 // without the parked sums and the second pass over U.  U* is read with ordinary loads

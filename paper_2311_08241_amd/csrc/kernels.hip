@@ -1400,84 +1400,84 @@ __global__ void __launch_bounds__(BLOCK) k_tile(TileArgs a) {
 // ---------------------------------------------------------------------------
 // Adjoint of one substep (reverse of the triangle and vertex phases)
 // ---------------------------------------------------------------------------
+// Reverse of one triangle's substep, shared by the per-substep and the tile kernels (equal
+// bit for bit).  wa..wc: dt_s lambda_eta / A at the vertices; ea..ec the forward elevations;
+// rH mean H0 (FP32: + eta_ref unless H is linear); mAe = -A_e; gd = g dt_s.  Updates the
+// adjoint transport (lx, ly), adds to the R gradient, returns the three slot terms and
+// lambda_H / 3.  The three gradients of a triangle sum to zero, so lambda_F and the slot
+// terms are formed from those of b and c alone; products that feed sums are fused
+// multiply-adds and divisions products with reciprocals (the gradients agree with the CPU
+// adjoint to rounding).  43 operations; 86 when every vector was formed and every product
+// rounded.
+template <typename T>
+__device__ __forceinline__ void adj_update(T wa, T wb, T wc, T ea, T eb, T ec, T rH, T gbx, T gby,
+                                           T gcx, T gcy, T mAe, T al, T rk, T gd, T dts, T th, T opt,
+                                           bool linear_h, T &lx, T &ly, T &grx, T &gry, T &pa,
+                                           T &pb, T &pc, T &chi) {
+    auto fma = [](T x, T y, T z) -> T {
+        if constexpr (sizeof(T) == 4) return __builtin_fmaf(x, y, z);
+        else return __builtin_fma(x, y, z);
+    };
+    const T third = T(1) / T(3);
+    // lambda_F = -sum_k w_k S_k,  S_k = -A_e grad N_k
+    const T vb = wa - wb, vc = wa - wc;
+    const T lFx = mAe * fma(vb, gbx, vc * gcx);
+    const T lFy = mAe * fma(vb, gby, vc * gcy);
+    const T lUnx = fma(opt, lFx, lx), lUny = fma(opt, lFy, ly);
+    // triangle quantities of the forward substep
+    const T db = eb - ea, dc = ec - ea;
+    const T gx = fma(db, gbx, dc * gcx);
+    const T gy = fma(db, gby, dc * gcy);
+    const T He = linear_h ? rH : fma(ea + eb + ec, third, rH);
+    // U' = C r with C = (I + aJ)^-1:  lambda_r = C^T lambda_U'
+    const T lrx = fma(-al, lUny, lUnx) * rk;
+    const T lry = fma(al, lUnx, lUny) * rk;
+    // r = (I - aJ) U + dt_s(-g H grad eta + R)
+    lx = fma(-th, lFx, fma(-al, lry, lrx));
+    ly = fma(-th, lFy, fma(al, lrx, lry));
+    grx = fma(dts, lrx, grx);
+    gry = fma(dts, lry, gry);
+    const T gHe = gd * He;
+    const T lgx = -gHe * lrx, lgy = -gHe * lry;
+    chi = -gd * third * fma(gx, lrx, gy * lry);
+    pb = fma(gbx, lgx, gby * lgy);
+    pc = fma(gcx, lgx, gcy * lgy);
+    pa = -(pb + pc);
+}
+
 // Reverse triangle phase for triangle e (any e; out of range returns).
 template <typename T, bool F32>
 __device__ __forceinline__ void adj_tri_at(const AdjArgs &a, int64_t e) {
     using T2 = typename Vec2<T>::type;
     if (e >= a.ne) return;
     const StepC &c = a.c;
-    const T dts = cdts<T>(c), g = cg<T>(c), th = cth<T>(c), opt = copt<T>(c);
+    const T dts = cdts<T>(c), th = cth<T>(c), opt = copt<T>(c);
+    const bool linear_h = (c.flags & KF_LINEAR_H) != 0;
     const T *geom = static_cast<const T *>(a.geom);
-    const T gbx = geom[e], gby = geom[a.ne + e], gcx = geom[2 * a.ne + e],
-            gcy = geom[3 * a.ne + e], Ae = geom[4 * a.ne + e];
-    const T gax = -(gbx + gcx), gay = -(gby + gcy);
     const int32_t v0 = a.tri[3 * e], v1 = a.tri[3 * e + 1], v2 = a.tri[3 * e + 2];
     const T *le = static_cast<const T *>(a.lam_eta);
     const T *Av = static_cast<const T *>(a.Av);
-    // lambda_F = -dt_s sum_k (lambda_eta_k / A_k) S_k,  S_k = -A_e grad N_k; the
-    // adjoint multiplies by reciprocals (1 / A_k, 1 / (1 + a^2), 1 / 3) where the
-    // forward divides: the gradients agree with the CPU adjoint to rounding, and the
-    // per-substep and tile kernels evaluate the same operations
-    T lFx = T(0), lFy = T(0);
-    {
-        const T w0 = -dts * le[v0] * (T(1) / Av[v0]);
-        lFx += w0 * (-Ae * gax);
-        lFy += w0 * (-Ae * gay);
-        const T w1 = -dts * le[v1] * (T(1) / Av[v1]);
-        lFx += w1 * (-Ae * gbx);
-        lFy += w1 * (-Ae * gby);
-        const T w2 = -dts * le[v2] * (T(1) / Av[v2]);
-        lFx += w2 * (-Ae * gcx);
-        lFy += w2 * (-Ae * gcy);
-    }
     T2 *lU = static_cast<T2 *>(a.lam_U);
     T2 lu = lU[e];
     if (a.lam_Uavg) {   // U^{m+1} enters the running sum with weight 1/M
         lu.x = lu.x + (T)(a.rM * a.lam_Uavg[2 * e]);
         lu.y = lu.y + (T)(a.rM * a.lam_Uavg[2 * e + 1]);
     }
-    const T lUnx = lu.x + opt * lFx, lUny = lu.y + opt * lFy;
-    T lUox = -th * lFx, lUoy = -th * lFy;
-    // triangle quantities of the forward substep
     const T *eta = static_cast<const T *>(a.eta_m);
     const T *H0 = static_cast<const T *>(a.H0);
-    const T ea = eta[v0], eb = eta[v1], ec = eta[v2];
-    const T db = eb - ea, dc = ec - ea;
-    const T gx = db * gbx + dc * gcx;
-    const T gy = db * gby + dc * gcy;
-    const T third = T(1) / T(3);
-    T He;
-    if (c.flags & KF_LINEAR_H) {
-        He = (H0[v0] + H0[v1] + H0[v2]) * third;
-    } else if (!F32) {
-        He = ((H0[v0] + ea) + (H0[v1] + eb) + (H0[v2] + ec)) * third;
-    } else {
-        He = ((H0[v0] + H0[v1] + H0[v2]) + (ea + eb + ec)) * third + c.eta_ref_f;
-    }
-    const T al = T(0.5) * static_cast<const T *>(a.f)[e] * dts;
-    const T rden = T(1) / (T(1) + al * al);
-    // U' = C r with C = (I + aJ)^-1:  lambda_r = C^T lambda_U'
-    const T lrx = (lUnx - al * lUny) * rden;
-    const T lry = (lUny + al * lUnx) * rden;
-    // r = (I - aJ) U + dt_s(-g H grad eta + R)
-    lUox += lrx - al * lry;
-    lUoy += lry + al * lrx;
+    T al, rk;
+    tri_consts<T>(static_cast<const T *>(a.f)[e], dts, al, rk);
     T2 *gR = static_cast<T2 *>(a.gR);
     T2 gr = gR[e];
-    gr.x += dts * lrx;
-    gr.y += dts * lry;
-    gR[e] = gr;
-    const T lgx = -dts * g * He * lrx, lgy = -dts * g * He * lry;
-    const T lHe = -dts * g * (gx * lrx + gy * lry);
     T *psi = static_cast<T *>(a.psi) + 4 * e;
-    psi[0] = gax * lgx + gay * lgy;
-    psi[1] = gbx * lgx + gby * lgy;
-    psi[2] = gcx * lgx + gcy * lgy;
-    psi[3] = lHe * third;
-    T2 lo;
-    lo.x = lUox;
-    lo.y = lUoy;
-    lU[e] = lo;
+    adj_update<T>(dts * le[v0] * (T(1) / Av[v0]), dts * le[v1] * (T(1) / Av[v1]),
+                  dts * le[v2] * (T(1) / Av[v2]), eta[v0], eta[v1], eta[v2],
+                  tri_mean_h<T>(H0[v0], H0[v1], H0[v2], linear_h, c), geom[e], geom[a.ne + e],
+                  geom[2 * a.ne + e], geom[3 * a.ne + e], -geom[4 * a.ne + e], al, rk,
+                  cg<T>(c) * dts, dts, th, opt, linear_h, lu.x, lu.y, gr.x, gr.y, psi[0], psi[1],
+                  psi[2], psi[3]);
+    gR[e] = gr;
+    lU[e] = lu;
 }
 
 template <typename T, bool F32>
@@ -1636,7 +1636,7 @@ __device__ __forceinline__ void adj_tile_body(const AdjTileArgs &a, int b, int G
     const T *lgeo = static_cast<const T *>(a.lgeo) + 4 * le0;
     const T *lae = static_cast<const T *>(a.lae) + le0;
     constexpr int OS = own_slots(EPT);
-    // den: 1 / (1 + a^2)
+    // den: 1 / (1 + a^2); g4: A_e, negated after the load
     T g0[EPT], g1[EPT], g2[EPT], g3[EPT], g4[EPT], lUx[EPT], lUy[EPT], al[EPT], den[EPT];
     T sux[EPT], suy[EPT];
     T grx[OS], gry[OS];
@@ -1748,8 +1748,8 @@ __device__ __forceinline__ void adj_tile_body(const AdjTileArgs &a, int b, int G
             }
             lUx[r] = u.x;
             lUy[r] = u.y;
-            al[r] = T(0.5) * fg[g] * dts;
-            den[r] = T(1) / (T(1) + al[r] * al[r]);   // reciprocal
+            tri_consts<T>(fg[g], dts, al[r], den[r]);
+            g4[r] = -g4[r];
             if (a.lam_Uavg) {   // U^{m+1} enters the running sum with weight 1/M
                 sux[r] = (T)(a.rM * a.lam_Uavg[2 * (int64_t)g]);
                 suy[r] = (T)(a.rM * a.lam_Uavg[2 * (int64_t)g + 1]);
@@ -1792,7 +1792,7 @@ __device__ __forceinline__ void adj_tile_body(const AdjTileArgs &a, int b, int G
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
-    const T g = cg<T>(c), th = cth<T>(c), opt = copt<T>(c);
+    const T gd = cg<T>(c) * dts, th = cth<T>(c), opt = copt<T>(c);
     const bool seeded = a.lam_Uavg != nullptr;
     for (int j = 0; j < cnt; ++j) {
         const int lev = cnt - j;
@@ -1811,61 +1811,33 @@ __device__ __forceinline__ void adj_tile_body(const AdjTileArgs &a, int b, int G
             const int le = tid + r * BLOCK;
             if (le >= ne_act) continue;
             const int ia = t0[r] & 0xffffu, ib = t0[r] >> 16, ic = t1[r] & 0xffffu;
-            const T gbx = g0[r], gby = g1[r], gcx = g2[r], gcy = g3[r], Ae = g4[r];
-            const T gax = -(gbx + gcx), gay = -(gby + gcy);
-            // lambda_F = -dt_s sum_k (lambda_eta_k / A_k) S_k,  S_k = -A_e grad N_k
-            T lFx = T(0), lFy = T(0);
-            {
-                const T w0 = -dts * sLe[ia] * sAv[ia];
-                lFx += w0 * (-Ae * gax);
-                lFy += w0 * (-Ae * gay);
-                const T w1 = -dts * sLe[ib] * sAv[ib];
-                lFx += w1 * (-Ae * gbx);
-                lFy += w1 * (-Ae * gby);
-                const T w2 = -dts * sLe[ic] * sAv[ic];
-                lFx += w2 * (-Ae * gcx);
-                lFy += w2 * (-Ae * gcy);
-            }
             T lux = lUx[r], luy = lUy[r];
             if (seeded) {
                 lux = lux + sux[r];
                 luy = luy + suy[r];
             }
-            const T lUnx = lux + opt * lFx, lUny = luy + opt * lFy;
-            T lUox = -th * lFx, lUoy = -th * lFy;
-            const T ea = em[ia], eb = em[ib], ec = em[ic];
-            const T db = eb - ea, dc = ec - ea;
-            const T gx = db * gbx + dc * gcx;
-            const T gy = db * gby + dc * gcy;
-            const T third = T(1) / T(3);
-            T He;
-            if (linear_h) {
-                He = (sH[ia] + sH[ib] + sH[ic]) * third;
-            } else if (!F32) {
-                He = ((sH[ia] + ea) + (sH[ib] + eb) + (sH[ic] + ec)) * third;
-            } else {
-                He = ((sH[ia] + sH[ib] + sH[ic]) + (ea + eb + ec)) * third + c.eta_ref_f;
-            }
-            const T lrx = (lUnx - al[r] * lUny) * den[r];
-            const T lry = (lUny + al[r] * lUnx) * den[r];
-            lUox += lrx - al[r] * lry;
-            lUoy += lry + al[r] * lrx;
+            T gqx = T(0), gqy = T(0), qa, qb, qc, chi;
             if (r < OS) {
-                grx[r < OS ? r : 0] += dts * lrx;
-                gry[r < OS ? r : 0] += dts * lry;
+                gqx = grx[r < OS ? r : 0];
+                gqy = gry[r < OS ? r : 0];
             }
-            const T lgx = -dts * g * He * lrx, lgy = -dts * g * He * lry;
-            const T lHe = -dts * g * (gx * lrx + gy * lry);
-            const T chi = lHe * third;
+            adj_update<T>(dts * sLe[ia] * sAv[ia], dts * sLe[ib] * sAv[ib], dts * sLe[ic] * sAv[ic], em[ia], em[ib],
+                          em[ic], tri_mean_h<T>(sH[ia], sH[ib], sH[ic], linear_h, c), g0[r], g1[r],
+                          g2[r], g3[r], g4[r], al[r], den[r], gd, dts, th, opt, linear_h, lux, luy,
+                          gqx, gqy, qa, qb, qc, chi);
+            if (r < OS) {
+                grx[r < OS ? r : 0] = gqx;
+                gry[r < OS ? r : 0] = gqy;
+            }
             const int p0 = t2[r] & 0xffffu, p1 = t2[r] >> 16, p2 = t1[r] >> 16;
-            sPsi[p0] = gax * lgx + gay * lgy;
-            sPsi[p1] = gbx * lgx + gby * lgy;
-            sPsi[p2] = gcx * lgx + gcy * lgy;
+            sPsi[p0] = qa;
+            sPsi[p1] = qb;
+            sPsi[p2] = qc;
             sChi[p0] = chi;
             sChi[p1] = chi;
             sChi[p2] = chi;
-            lUx[r] = lUox;
-            lUy[r] = lUoy;
+            lUx[r] = lux;
+            lUy[r] = luy;
         }
         lds_barrier();
         // vertex phase: lambda_eta += sum over the vertex's triangles (ascending) of

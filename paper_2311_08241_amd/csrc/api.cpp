@@ -1591,11 +1591,36 @@ se_status se_subcycle_adjoint(se_mesh *m, const se_params *p, const void *eta0, 
     const int64_t nv = m->h.nv, ne = m->h.ne;
     const size_t es = f32 ? 4 : 8;
     const Layout L = fwd_layout(nv, ne, f32, nsub, vol_width(nv));
-    const AdjLayout A = adj_layout(nv, ne, f32, nsub, ckpt_every, L.total);
+    AdjLayout A = adj_layout(nv, ne, f32, nsub, ckpt_every, L.total);
     char *w = static_cast<char *>(ws);
     const size_t st_bytes = al((nv + 2 * ne) * es);
     auto st_eta = [&](size_t off) { return w + off; };
     auto st_U = [&](size_t off) { return w + off + nv * es; };
+
+    // the caller's plan, or a default that the forward subcycle made: the form's own where
+    // it runs the reverse kernel, else the one for every form
+    const DevTiles *TP = m->plan.get();
+    if (!TP) {
+        std::lock_guard<std::mutex> lk(m->plan_mu);
+        TP = m->dflt[CL_FB + (f32 ? 1 : 0)].get();
+        if (!TP || !TP->adj_ready[f32 ? 1 : 0]) TP = m->dflt[CL_ANY].get();
+    }
+    const bool fwd_tiles = TP && TP->ok(f32, false) && TP->prepared[f32 ? 1 : 0];
+    const bool rev_tiles = fwd_tiles && TP->adj_ready[f32 ? 1 : 0];
+    // The reverse tile kernel reads the forward elevations alone, a fifth of a state or
+    // less.  Where those of all substeps and two states for the forward launches to
+    // alternate between fit the bytes that the checkpoints and segment buffers of this
+    // ckpt_every take, the step is one segment: no substep runs forward twice and the
+    // reverse launches are not cut at checkpoints (always so up to about 180 substeps;
+    // 65,536 vertices FP64, M = 30, ckpt_every 5, one gradient: 220 -> 154 us).
+    const size_t whole = al(static_cast<size_t>(nsub) * nv * es) + 2 * st_bytes;
+    if (rev_tiles && A.nseg > 1 && A.ckpt + whole <= A.lam_eta) {
+        A.k = nsub;
+        A.nseg = 1;
+        A.etraj = A.ckpt;
+        A.traj[0] = A.lam_eta - 3 * st_bytes;   // slot 1 of either is all that is used
+        A.traj[1] = A.lam_eta - 2 * st_bytes;
+    }
 
     // forward substep (state update only) on the plain path
     PlainArgs fa{};
@@ -1644,15 +1669,7 @@ se_status se_subcycle_adjoint(se_mesh *m, const se_params *p, const void *eta0, 
     auto seg_U = [&](int32_t sg, int32_t j) -> const void * {
         return j == 0 ? ckpt_U(sg) : st_U(seg_off(sg, j));
     };
-    // the caller's plan, or a default that the forward subcycle made: the form's own where
-    // it runs the reverse kernel, else the one for every form
-    const DevTiles *TP = m->plan.get();
-    if (!TP) {
-        std::lock_guard<std::mutex> lk(m->plan_mu);
-        TP = m->dflt[CL_FB + (f32 ? 1 : 0)].get();
-        if (!TP || !TP->adj_ready[f32 ? 1 : 0]) TP = m->dflt[CL_ANY].get();
-    }
-    if (TP && TP->ok(f32, false) && TP->prepared[f32 ? 1 : 0]) {
+    if (fwd_tiles) {
         // The mesh has a tile plan for this precision: each segment runs as temporally
         // blocked launches from checkpoint q to checkpoint q + 1 (the tile path equals
         // the plain path bit for bit).  A segment is a subcycle of k substeps of this
@@ -1714,7 +1731,7 @@ se_status se_subcycle_adjoint(se_mesh *m, const se_params *p, const void *eta0, 
     aa.rM = 1.0 / static_cast<double>(nsub);
     aa.thrM = p->theta * aa.rM;
 
-    if (TP && TP->ok(f32, false) && TP->prepared[f32 ? 1 : 0] && TP->adj_ready[f32 ? 1 : 0]) {
+    if (rev_tiles) {
         // 2'. reverse sweep on the tile plan, segment by segment from the last.  A
         // segment's forward elevations are recomputed from its checkpoint on the tile
         // kernel (mode 3: each substep's owned elevations to the segment's trajectory
@@ -1734,7 +1751,7 @@ se_status se_subcycle_adjoint(se_mesh *m, const se_params *p, const void *eta0, 
         auto traj_of = [&](int32_t sg) { return static_cast<void *>(w + A.etraj + (sg & 1) * traj_bytes); };
         AdjTileArgs ra{};
         ra.hdr = P.hdr.as<const TileHdrK>();
-            ra.lv_gid = P.lv_gid.as<const int32_t>();
+        ra.lv_gid = P.lv_gid.as<const int32_t>();
         ra.le_rec = P.le_rec.as<const uint32_t>();
         ra.le_pos = P.le_pos.as<const uint32_t>();
         ra.le_gid = P.le_gid.as<const int32_t>();

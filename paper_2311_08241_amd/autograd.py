@@ -24,6 +24,9 @@ class SubcycleFn(torch.autograd.Function):
         ctx.save_for_backward(eta0.detach(), U0.detach(), R.detach(), H0.detach(), f.detach())
         ctx.W = None if W is None else W.detach()
         ctx.cfg = (mesh, params, nsub, dt, ckpt_every)
+        # an output that the loss does not use has no seed: the adjoint reads a null seed as
+        # zero, where filled zeros would be read by every reverse launch
+        ctx.set_materialize_grads(False)
         return eta, U, Uavg
 
     @staticmethod

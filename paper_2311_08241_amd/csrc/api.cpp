@@ -201,6 +201,15 @@ se_status plan_host(const std::vector<const HostMesh *> &members, const std::vec
     return SE_OK;
 }
 
+// The reverse tile kernel has a variant for a plan of these sizes: up to four triangles per
+// thread, with 1024-thread workgroups three in FP32 and two in FP64; a tile's owned vertices
+// within two per thread; its LDS within 160 KiB.
+bool adj_fits(bool f32, int32_t max_nv, int32_t max_nvu, int32_t max_cs, int32_t T, int32_t K,
+              int32_t block, int32_t ept) {
+    return ept >= 1 && ept <= (block < 1024 ? 4 : f32 ? 3 : 2) && T <= 2 * block &&
+           adj_tile_lds_bytes(f32, block, K, max_nv, max_nvu, max_cs) <= 160 * 1024;
+}
+
 // Upload a tile plan built by plan_host (ht is used up).
 se_status upload_plan(const std::vector<const HostMesh *> &members, const std::vector<int64_t> &voff,
                       const std::vector<int64_t> &eoff, int32_t T, int32_t K, int32_t block,
@@ -316,15 +325,13 @@ se_status upload_plan(const std::vector<const HostMesh *> &members, const std::v
     for (int f = 0; f < 2; ++f)
         p->prepared[f] = p->ok(f == 1, false) && prepare_tile(f == 1, 0, p->ept, p->block) == hipSuccess;
     // the adjoint on the plan: recompute with trajectory output (mode 3) and the reverse
-    // tile kernel (up to four triangles per thread, with 1024-thread workgroups three in
-    // FP32 and two in FP64; a tile's owned vertices within two per thread, its LDS within
-    // 160 KiB)
+    // tile kernel
     for (int f = 0; f < 2; ++f) {
         const bool f32 = f == 1;
         p->lds_adj[f] = static_cast<size_t>(adj_tile_lds_bytes(f32, block, K, p->max_nv,
                                                                p->max_nvu, p->max_cs));
-        p->adj_ready[f] = p->prepared[f] && ept <= 4 &&
-                          T <= 2 * block && p->lds_adj[f] <= 160 * 1024 &&
+        p->adj_ready[f] = p->prepared[f] &&
+                          adj_fits(f32, p->max_nv, p->max_nvu, p->max_cs, T, K, block, ept) &&
                           prepare_tile(f32, 3, ept, block) == hipSuccess &&
                           prepare_adj_tile(f32, ept, block) == hipSuccess;
     }
@@ -600,7 +607,7 @@ se_status check_device(const se_mesh *m) {
 }
 
 // Forms of the subcycle that a default plan is chosen for.
-enum : int { CL_FB = 0, CL_SESM = 2, CL_VISC = 4, CL_ANY = 6 };   // + 1: FP32; ANY: every form
+enum : int { CL_FB = 0, CL_SESM = 2, CL_VISC = 4, CL_ADJ = 6, CL_ANY = 8 };   // + 1: FP32; ANY: every form
 
 bool plan_fits(int cl, const HostTiles &ht, const se_plan_stats_t &st, int32_t K, int32_t block) {
     const bool f32 = cl & 1;
@@ -611,6 +618,9 @@ bool plan_fits(int cl, const HostTiles &ht, const se_plan_stats_t &st, int32_t K
             return (f32 ? st.ok_f32 : st.ok_f64) && K >= 2 &&
                    visc_lds(f32 ? st.lds_f32 : st.lds_f64, f32, ht.max_ne) <= 160 * 1024 &&
                    visc_regs_ok(f32, block, st.tri_per_thread);
+        case CL_ADJ:
+            return (f32 ? st.ok_f32 : st.ok_f64) &&
+                   adj_fits(f32, ht.max_nv, ht.max_nvu, ht.max_cs, ht.T, K, block, st.tri_per_thread);
         default: return st.ok_f32 && st.ok_f64 && st.ok_sesm_f32 && st.ok_sesm_f64;
     }
 }
@@ -637,6 +647,12 @@ struct PlanCand {
 //                     550,482: 525, 852   979,989: 869, 1448
 //   AB3-AM4           11,397: 116, 129   195,440: 275, 511   550,482: 674, 1512
 //   viscous           11,397: 210, 241   195,440: 595, 1108   550,482: 1577, 3074
+// The adjoint's (a gradient of 30 substeps, forward sweep included, us) has two triangles per
+// thread in FP64, which is what its registers allow at 1024 threads:
+//   2,048: 87, 94   65,536: 124, 154   104,000: 164, 238   202,500: 257, 460
+//   490,000: 574, 1118
+// and, without a plan of its own, ran the per-substep kernels wherever the forward plan was
+// not one for its kernel: 104,000 vertices FP64 809, 490,000 650 and 3,377.
 // One list for every mesh and form (512,4,512 on most) took e.g. 145 FP64 at 11,397
 // vertices and 37 substeps (81 now), 1,140 viscous FP32 at 196,608 (611).
 std::vector<PlanCand> default_plans(int cl, int64_t nv) {
@@ -694,6 +710,25 @@ std::vector<PlanCand> default_plans(int cl, int64_t nv) {
             if (nv <= 400000) rounds(392, {6, 4}, 512, 4);
             c.push_back({448, 4, 512, 4, 0});
             c.push_back({384, 4, 512, 4, 0});
+            break;
+        case CL_ADJ + 1:
+            if (tiny) c.push_back({64, 6, 512, 2, 0});
+            if (nv <= 288 * 256) rounds(288, {6}, 1024, 2);
+            if (nv <= 480 * 256) rounds(480, {8, 6, 5}, 1024, 3);
+            else if (nv <= 300000) rounds(800, {4, 3}, 1024, 3);
+            c.push_back({416, 4, 512, 4, 0});
+            c.push_back({256, 4, 512, 4, 0});
+            c.push_back({128, 4, 512, 4, 0});
+            break;
+        case CL_ADJ:
+            if (tiny) c.push_back({64, 6, 512, 2, 0});
+            if (nv <= 288 * 256) rounds(288, {6, 5}, 1024, 2);
+            if (nv <= 464 * 256) rounds(464, {4}, 1024, 2);
+            else if (nv <= 528 * 256) rounds(528, {3}, 1024, 2);
+            rounds(464, {4}, 1024, 2);
+            c.push_back({416, 4, 1024, 2, 0});
+            c.push_back({256, 4, 512, 4, 0});
+            c.push_back({128, 4, 512, 4, 0});
             break;
         default: break;
     }
@@ -758,6 +793,13 @@ se_status mesh_plan(se_mesh *m, int cl, bool may_alloc, hipStream_t s, DevTiles 
     std::unique_ptr<DevTiles> p;
     bool any_ok = false;
     auto cand = default_plans(cl, m->h.nv);
+    if ((cl & ~1) == CL_ADJ) {   // none fits: the forward plans are asked
+        if (make_default(m, cl, cand, p, nullptr) == SE_OK) {
+            m->dflt[cl] = std::move(p);
+            *out = m->dflt[cl].get();
+        }
+        return SE_OK;
+    }
     cand.insert(cand.end(), kAnyPlans.begin(), kAnyPlans.end());
     SE_TRY(make_default(m, cl, cand, p, &any_ok));
     if (!any) {
@@ -1597,12 +1639,21 @@ se_status se_subcycle_adjoint(se_mesh *m, const se_params *p, const void *eta0, 
     auto st_eta = [&](size_t off) { return w + off; };
     auto st_U = [&](size_t off) { return w + off + nv * es; };
 
-    // the caller's plan, or a default that the forward subcycle made: the form's own where
-    // it runs the reverse kernel, else the one for every form
+    // the caller's plan; else, once a forward subcycle has made a default, the adjoint's own;
+    // else (it may not be made now, or none fits) the forward one's where it runs the reverse
+    // kernel, or the one for every form
     const DevTiles *TP = m->plan.get();
     if (!TP) {
+        bool planned;
+        {
+            std::lock_guard<std::mutex> lk(m->plan_mu);
+            planned = m->dflt[CL_ANY] != nullptr;
+        }
+        DevTiles *own = nullptr;
+        if (planned) SE_TRY(mesh_plan(m, CL_ADJ + (f32 ? 1 : 0), true, s, &own));
         std::lock_guard<std::mutex> lk(m->plan_mu);
-        TP = m->dflt[CL_FB + (f32 ? 1 : 0)].get();
+        TP = own;
+        if (!TP || !TP->adj_ready[f32 ? 1 : 0]) TP = m->dflt[CL_FB + (f32 ? 1 : 0)].get();
         if (!TP || !TP->adj_ready[f32 ? 1 : 0]) TP = m->dflt[CL_ANY].get();
     }
     const bool fwd_tiles = TP && TP->ok(f32, false) && TP->prepared[f32 ? 1 : 0];

@@ -178,9 +178,9 @@ struct se_mesh {
     sesub::DevMesh d;
     std::unique_ptr<sesub::DevTiles> plan;      // the caller's (se_set_plan)
     // defaults made on first use while the caller has set none: per form of the subcycle
-    // (forward-backward, AB3-AM4, viscous; FP64, FP32), and one that runs every form
+    // (forward-backward, AB3-AM4, viscous, the adjoint; FP64, FP32), and one that runs every form
     // (one of the others where that runs them all)
-    std::shared_ptr<sesub::DevTiles> dflt[7];
+    std::shared_ptr<sesub::DevTiles> dflt[9];
     std::mutex plan_mu;                         // guards dflt
     int32_t plan_T = 1024, plan_K = 4, plan_block = 256;
 };

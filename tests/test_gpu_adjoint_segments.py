@@ -38,3 +38,26 @@ def test_whole_trajectory_and_segments_equal_the_per_substep_path(precision, pla
         assert mesh.check_faults() == 0
     for a, b in zip(*out):
         assert torch.isfinite(a).all() and torch.equal(a, b)
+
+
+# one tile per 64 vertices, one tile per CU, 1024-thread tiles of two rounds (FP64) or one
+@pytest.mark.parametrize("n", [64, 250, 360])
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+def test_default_plan_of_the_adjoint_equals_the_per_substep_path(precision, n):
+    from paper_2311_08241_amd import Mesh, Params, device_inputs
+    case = sesynth.adjoint_c5(n=n)
+    out = []
+    for planned in (False, True):
+        mesh = Mesh.from_dict(case, device=0)
+        p = Params(precision=precision, eta_ref=case["eta_ref"] if precision == "f32" else 0.0)
+        d = device_inputs(mesh, case, p)
+        if planned:   # a forward step makes the mesh's default plans
+            mesh.subcycle(d["eta"].clone(), d["U"].clone(), R=d["R"], f=d["f"], H0=d["H0"],
+                          nsub=4, dt=case["tau"] / 8, params=p)
+        lam = torch.linspace(0.5, 1.5, mesh.nv, dtype=p.dtype, device="cuda:0")
+        out.append(mesh.adjoint(d["eta"], d["U"], R=d["R"], f=d["f"], H0=d["H0"], nsub=13,
+                                dt=case["tau"] / 4, params=p, ckpt_every=5, lam_eta=lam))
+        torch.cuda.synchronize()
+        assert mesh.check_faults() == 0
+    for a, b in zip(*out):
+        assert torch.isfinite(a).all() and torch.equal(a, b)

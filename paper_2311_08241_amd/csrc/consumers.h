@@ -59,6 +59,7 @@ struct ForcingArgs {
     double Cd;
     const int32_t *nlev;        // [ne] or null (K everywhere)
     const double *RA, *RP, *RhV, *u;   // [ne][K][2], any may be null
+    const double *col[3];       // those of the first three that are not null (set at launch)
     const double *tau_s;        // [ne][2] or null
     void *R;                    // [ne][2] double or float
     uint32_t *faults;

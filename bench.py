@@ -236,12 +236,13 @@ def bench_adjoint(args, log):
             mesh.set_plan(*plan)
             ws = mesh.workspace(p, case["nsub"], case["ckpt_every"])
         # tile plans for this mesh (shapes that give 64-512 tiles, with 2-6 substeps per
-        # launch; 5 or more run a checkpoint segment in one launch): the forward and the
-        # adjoint are each timed on every plan and each is reported at its fastest
+        # launch): the forward and the adjoint are each timed on every plan and each is
+        # reported at its fastest
         bestf = besta = None
         for plan in ((1024, 4, 512), (512, 4, 512), (256, 4, 256), (128, 4, 256),
                      (256, 5, 256), (128, 5, 256), (128, 6, 256), (256, 5, 512),
-                     (192, 5, 512), (320, 5, 512), (128, 5, 512), (256, 5, 1024)):
+                     (192, 5, 512), (320, 5, 512), (128, 5, 512), (256, 5, 1024),
+                     (256, 6, 1024)):
             if not mesh.plan_stats(*plan)["ok_f32" if prec == "f32" else "ok_f64"]:
                 continue
             use(plan)
@@ -278,18 +279,10 @@ def bench_adjoint(args, log):
         fwd()
         msf = _time(fwd, 5)
         # launches in stream order, each waiting for the previous one (the tile path of
-        # se_subcycle_adjoint): the sweep up to the last checkpoint, ceil(k / k_fused)
-        # tile launches per segment; the last segment's recompute; per segment its
-        # reverse launches (ceil(len / k_fused)), the recompute of the segment before it
-        # sharing them (the first reverse launch starts from the seeds, the last one
-        # writes the gradients of the initial state)
-        nsub, k = case["nsub"], case["ckpt_every"]
-        K = besta[1][1]
-        segs = [min(k, nsub - m0) for m0 in range(0, nsub, k)]
-        nch = lambda L: -(-L // K)
-        rec = lambda L: nch(L) if L > 1 else 0
-        nops = (nch(k) * (len(segs) - 1) + rec(segs[-1])
-                + sum(max(nch(L), rec(segs[i - 1]) if i > 0 else 0) for i, L in enumerate(segs)))
+        # se_subcycle_adjoint; the elevations of the whole step fit the checkpoints' bytes):
+        # the forward sweep that keeps them, then the reverse launches, ceil(nsub / k_fused)
+        # each
+        nops = 2 * -(-case["nsub"] // besta[1][1])
         out[prec] = {"plan": list(besta[1]), "forward_plan": list(bestf[1]),
                      "ms_adjoint": ms, "ms_adjoint_graph": ms_graph, "ms_forward": msf,
                      "adjoint_over_forward": ms / msf, "dependent_launches": nops,

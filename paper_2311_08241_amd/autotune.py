@@ -65,18 +65,19 @@ _F64_VGPRS = {1: 82, 2: 101, 3: 127, 4: 157, 6: 215, 8: 256}
 # registers; the tiers the library refuses are never timed)
 _VISC_VGPRS = {"f32": {1: 72, 2: 102, 3: 127, 4: 141, 6: 189, 8: 239},
                "f64": {1: 109, 2: 141, 3: 165, 4: 197, 6: 256, 8: 256}}
+# FP32 AB3-AM4 (four slots re-materialise their packed indices)
+_SESM32_VGPRS = {1: 65, 2: 89, 3: 111, 4: 124, 6: 188, 8: 240}
 
 
 def _vgprs(precision: str, ept: int) -> int:
     """Approximate VGPRs of the tile kernel per register tier (measured from the
-    compiler's resource report: about 24 per triangle slot in FP32, 26 with the two
-    extra transports of the AB3-AM4 scheme, 51 in FP64 AB3-AM4; FP64 forward-backward
-    and viscous tiers tabulated)."""
+    compiler's resource report: about 24 per triangle slot in FP32, 51 in FP64 AB3-AM4;
+    FP64 forward-backward, FP32 AB3-AM4 and viscous tiers tabulated)."""
     prec, sm = _split(precision)
     if _visc(precision):
         v = _VISC_VGPRS[prec][ept]
     elif prec == "f32":
-        v = 37 + 26 * ept if sm else 32 + 24 * ept
+        v = _SESM32_VGPRS[ept] if sm else 32 + 24 * ept
     else:
         v = 52 + 51 * ept if sm else _F64_VGPRS[ept]
     return -(-v // 8) * 8

@@ -24,7 +24,7 @@
  *  - "device" pointers are HIP device memory of the device the mesh was
  *    created on; "host" pointers are ordinary host memory.  The library never
  *    frees caller memory.  Meshes, batches and plans own their own device
- *    arrays (allocated at creation or at se_set_plan, freed at destroy).
+ *    arrays (allocated at creation, at se_set_plan or with a default plan, freed at destroy).
  *  - Field arrays are in the mesh's internal (reordered) numbering; the
  *    permutations from se_mesh_perm map it to the caller's numbering.
  *  - Element type follows se_params.precision: SE_F64 -> double for eta, U,
@@ -231,10 +231,13 @@ se_status se_subcycle_plain(se_mesh *mesh, const se_params *params, se_state *st
 /* Adjoint of se_subcycle.  For the scalar
  *   J = <lam_eta, eta^M> + <lam_U, U^M> + <lam_Uavg, <<U>>>
  * (plain sums over array entries) writes dJ/d eta^0, dJ/d U^0, dJ/dR, dJ/dH0.
- * Seeds may be NULL (zero); outputs may be NULL (not computed).  The forward
- * trajectory is recomputed from checkpoints stored every ckpt_every substeps
- * (1 <= ckpt_every <= nsub); each segment's recompute runs in the same launches
- * as the reverse substeps of the segment after it.  eta0/U0 are the forward inputs and are not
+ * Seeds may be NULL (zero); outputs may be NULL (not computed).  ckpt_every
+ * (1 <= ckpt_every <= nsub) sets the workspace: a checkpoint every ckpt_every substeps
+ * and two segments of states.  On a tile plan the forward elevations of all substeps are
+ * kept instead where they fit that workspace (up to about 180 substeps for any
+ * ckpt_every); else the trajectory is recomputed from the checkpoints, each segment in the
+ * same launches as the reverse substeps of the segment after it.  Gradients do not depend
+ * on it.  eta0/U0 are the forward inputs and are not
  * modified.  Element types follow params.precision; lam_Uavg is double. */
 se_status se_subcycle_adjoint(se_mesh *mesh, const se_params *params, const void *eta0,
                               const void *U0, const se_forcing *forcing, int32_t nsub,
@@ -265,6 +268,10 @@ se_status se_subcycle_batched(se_batch *batch, const se_params *params, se_state
 /* Execution plan of the temporally blocked kernel: tile = vertices per
  * tile (64..8192), k_fused = substeps per launch (1..8), block = threads per
  * workgroup (256, 512 or 1024).  Applies to a mesh (kind 0) or a batch (kind 1).
+ * Without one, each form of the subcycle makes a default plan from the number of vertices
+ * at its first call (the adjoint once a forward call has made one; per-substep kernels
+ * before); se_set_plan replaces them all.  The fields do not depend on the plan, the
+ * volume to rounding.
  * Returns SE_ERR_ARG if the plan does not fit the kernel's register or LDS
  * budget for this mesh. */
 se_status se_set_plan(void *mesh_or_batch, int32_t kind, int32_t tile, int32_t k_fused,

@@ -768,7 +768,7 @@ se_status make_default(se_mesh *m, int cl, const std::vector<PlanCand> &cand,
 // made at its first call, else (nothing may be allocated: se_subcycle_noalloc, or a stream
 // under capture once some default exists) one that runs every form.  The first default of
 // a mesh brings such a plan along, so a call that found a plan before still finds one.
-// Results do not depend on the plan.
+// The fields do not depend on the plan, the volume to rounding.
 se_status mesh_plan(se_mesh *m, int cl, bool may_alloc, hipStream_t s, DevTiles **out) {
     *out = nullptr;
     if (m->plan) {
@@ -1058,12 +1058,20 @@ static se_status check_state(const se_state *st, const se_forcing *fo, const voi
 }
 
 // Access policy of the tile kernels for nv vertices: stream each tile's own tables and
-// the write-back past the caches when one launch moves more than half of the 256 MiB
-// last-level cache (about 236 B per vertex in FP32, 356 in FP64); smaller working sets
-// stay cached from launch to launch and keep ordinary accesses (lat-lon workload, 2.2M
-// vertices: 150 -> 136 us per launch with it; the 65k-vertex adjoint basin 10% slower).
-static int32_t stream_policy(int64_t nv, bool f32) {
-    return (f32 ? 236.0 : 356.0) * static_cast<double>(nv) > 128.0 * 1024 * 1024 ? 1 : 0;
+// the write-back past the caches when one launch's working set exceeds the 256 MiB
+// last-level cache (about 236 B per vertex in FP32, 356 in FP64; half more with the state of
+// AB3-AM4 or the tables of the viscous term, wide); smaller ones stay cached from launch to
+// launch and keep ordinary accesses.  60 substeps, us, ordinary / streamed:
+//   SE FP32 900,000 vertices 797 / 849, 1,210,000 1118 / 1087, 1,380,000 1298 / 1198
+//   SE FP64 550,482 795 / 839, 702,000 1049 / 1128, 801,000 1230 / 1240, 900,000 1417 / 1392
+//   AB3-AM4 FP32 702,000 874 / 919, 801,000 1034 / 1024, 900,000 1170 / 1125
+//   AB3-AM4 FP64 384,000 1022 / 1085, 524,288 1645 / 1590, 630,000 1984 / 1854
+//   viscous FP32 702,000 2200 / 2274, 801,000 2505 / 2495, 900,000 2916 / 2787
+//   viscous FP64 384,000 2351 / 2403, 524,288 3317 / 3228, 630,000 4045 / 3817
+// (the line lay at half the cache for all forms).
+static int32_t stream_policy(int64_t nv, bool f32, bool wide) {
+    return (f32 ? 236.0 : 356.0) * (wide ? 1.5 : 1.0) * static_cast<double>(nv) >
+           256.0 * 1024 * 1024;
 }
 
 // Launch arguments of the tile kernel on one mesh: plan tables, forcing, workspace
@@ -1071,7 +1079,7 @@ static int32_t stream_policy(int64_t nv, bool f32) {
 static TileArgs tile_args(const se_mesh *m, const DevTiles &P, bool f32, const se_forcing *fo,
                           char *w, const Layout &L, const StepC &c) {
     TileArgs a{};
-    a.nt = stream_policy(m->h.nv, f32);
+    a.nt = stream_policy(m->h.nv, f32, false);
     a.hdr = P.hdr.as<const TileHdrK>();
     a.lv_gid = P.lv_gid.as<const int32_t>();
     a.le_rec = P.le_rec.as<const uint32_t>();
@@ -1182,6 +1190,7 @@ se_status sesub::subcycle_tile(se_mesh *m, const se_params *p, se_state *st,
     c.vol_off = 0;
 
     TileArgs a = tile_args(m, P, f32, fo, w, L, c);
+    a.nt = stream_policy(nv, f32, sm || visc);
     a.Uavg = st->Uavg;
     a.ksub = visc ? P.K / 2 : P.K;
     void *eta_u = st->eta, *U_u = st->U;
@@ -2292,7 +2301,7 @@ se_status se_subcycle_batched(se_batch *b, const se_params *p, se_state *st, con
     }
     char *w = static_cast<char *>(ws);
     TileArgs a{};
-    a.nt = stream_policy(b->nv, f32);
+    a.nt = stream_policy(b->nv, f32, false);
     a.hdr = P.hdr.as<const TileHdrK>();
     a.lv_gid = P.lv_gid.as<const int32_t>();
     a.le_rec = P.le_rec.as<const uint32_t>();

@@ -285,21 +285,30 @@ __global__ void __launch_bounds__(256) k_zstar_w(TrimArgs a, const double *S) {
 // The arithmetic of k_zstar_h + k_trim + k_zstar_w in the same order (the same bits),
 // without the parked sums and the second pass over U.  U* is read with ordinary loads
 // (the tiles after it find the shared triangles in L2); U, hnew and w are written once.
+//
+// Bound: memory, behind a chain of dependent loads per workgroup.  Everything that the
+// header alone addresses (records, ids, row bounds and entries) is loaded in one round, and
+// everything that those address (columns, U*, <<U>>, flux vectors) in a second, without a
+// branch between the loads of a round; one after the other they made about eight round
+// trips of a workgroup's 20 us.  550k vertices: K = 8 202 -> 138 us, K = 24 336 -> 311,
+// K = 40 536 -> 480 (4.4 TB/s of 5.0 that a copy reaches), K = 56 807 -> 704.
 // ---------------------------------------------------------------------------
 constexpr int TT_VPG = kTrimTileOwn / 32;   // own vertices per group
 
 // triangles per group: the trimmed transports of a group's triangles sit in registers
-// (4 TPG L VGPRs); kept near 128 VGPRs so that four workgroups share a CU (at K = 40,
-// 64-triangle tiles ran 8% faster than 96-triangle ones despite their larger halo)
-template <int L> constexpr int trim_tpg() { return L <= 1 ? 8 : L <= 3 ? 4 : L <= 4 ? 3 : 2; }
+// (4 TPG L VGPRs), beside a round's loads; within 128 VGPRs up to L = 5, so that four
+// workgroups share a CU, within 168 beyond (three).  64-triangle tiles ran 8% faster than
+// 96-triangle ones at K = 40 despite their larger halo; with one triangle per group more at
+// L = 3 and 4 the rounds spill (550k vertices: K = 24 347 us, 311 now; K = 32 442, 388).
+template <int L> constexpr int trim_tpg() { return L <= 1 ? 8 : L <= 2 ? 4 : L <= 3 ? 3 : 2; }
 
 // Layer blocks per round of step 3 and the doubles of the vertex columns or a round's
 // transports, whichever are more (the transports lie over the columns, which step 2 has
 // used up): as few rounds as leave room for four workgroups per CU (40 KB of LDS each), of
 // even sizes.  K = 40 takes its five blocks as three and two: 4 barriers and 2 readings of
 // every row entry instead of 10 and 5, in less LDS (550k vertices: 557 -> 537 us).  Three
-// blocks of 128-triangle tiles would leave two workgroups per CU (K = 24, 550k vertices:
-// 336 us; 465 with three, 390 with one block per round).
+// blocks of 128-triangle tiles would leave two workgroups per CU (K = 24, 550k vertices,
+// before the loads were batched: 336 us; 465 with three, 390 with one block per round).
 template <int L> constexpr int trim_nb() {
     constexpr int CE = 32 * trim_tpg<L>();
     constexpr int fit = (40 * 1024 - CE * 54) / (CE * 128), most = fit < 1 ? 1 : fit < L ? fit : L;
@@ -312,13 +321,15 @@ template <int L, int TPG> __host__ __device__ constexpr size_t trim_cols(int cap
 }
 
 template <int L, int TPG>
-__global__ void __launch_bounds__(256) k_trim_tile(TrimArgs a, const double *S) {
+__global__ void __launch_bounds__(256, L >= 2 && L <= 5 ? 4 : 3)
+    k_trim_tile(TrimArgs a, const double *S) {
     extern __shared__ __align__(16) double tsm[];
     const int tid = threadIdx.x, g = tid & 7, grp = tid >> 3;
     const int K = a.K;
     const int32_t *hd = a.tt_hdr + 8 * xcd_block();
-    const int32_t v0 = hd[0], nvo = hd[1], nvl = hd[2], nel = hd[3], neo = hd[4];
-    const int32_t lv_off = hd[5], le_off = hd[6], nent = hd[7];
+    const int32_t v0 = hd[0], nvo = hd[1] & 0xffff, nvl = hd[1] >> 16;
+    const int32_t nel = hd[2] & 0xffff, neo = hd[2] >> 16;
+    const int32_t lv_off = hd[3], le_off = hd[4], nent = hd[5], jb = hd[6];
     constexpr int CE = 32 * TPG;
     constexpr int NB = trim_nb<L>();
     double *sP = tsm;                             // [cap_v][K], then, over it,
@@ -326,60 +337,135 @@ __global__ void __launch_bounds__(256) k_trim_tile(TrimArgs a, const double *S) 
     d2v *sS = reinterpret_cast<d2v *>(tsm + trim_cols<L, TPG>(a.tt_cap_v, K));   // [3 CE]
     uint16_t *sL = reinterpret_cast<uint16_t *>(sS + 3 * CE);             // [3 CE]
     const double inv_tau = 1.0 / a.tau;
-    // the loads of steps 2 and 3 that do not wait for LDS, issued first: the local
-    // triangles' records, transports U* and <<U>> (past the tile's last triangle a group
-    // repeats it and stores nothing), the own vertices' row bounds
+    // Round A, what the header alone gives: records of the local triangles (past the tile's
+    // last one a group repeats it and stores nothing), ids of the first other vertices, the
+    // own vertices' row bounds, the rows' local triangles and table columns.
+    // own / other vertices per group whose columns round B loads (as registers allow)
+    constexpr int OB = L <= 2 ? TT_VPG : L <= 5 ? 1 : 0;
+    constexpr int HB = L <= 1 ? 2 : 0;
+    constexpr int EI = (3 * CE + 255) / 256;
+    int2 rec[TPG];
+#pragma unroll
+    for (int q = 0; q < TPG; ++q) rec[q] = a.tt_le[le_off + max(min(grp + 32 * q, nel - 1), 0)];
+    int32_t vs[OB + HB + 1];
+#pragma unroll
+    for (int q = 0; q < OB; ++q) vs[q] = v0 + min(grp + 32 * q, nvo - 1);
+#pragma unroll
+    for (int q = 0; q < HB; ++q) {
+        const int h = min(grp + 32 * q, nvl - nvo - 1);
+        vs[OB + q] = a.tt_lv[lv_off + max(h, 0)];   // none: the next tile's, or the padding
+    }
+    int j0[TT_VPG], j1[TT_VPG];
+    auto row_bounds = [&] {
+#pragma unroll
+        for (int q = 0; q < TT_VPG; ++q) {
+            const int64_t v = v0 + min(grp + 32 * q, nvo - 1);
+            j0[q] = a.row_ptr[v];
+            j1[q] = a.row_ptr[v + 1];
+        }
+    };
+    if constexpr (L <= 7) row_bounds();
+    uint16_t rl[EI];
+    int32_t pc[EI];
+#pragma unroll
+    for (int n = 0; n < EI; ++n) {
+        const int64_t i = min<int64_t>(jb + max(min(tid + 256 * n, nent - 1), 0), 3 * a.ne - 1);
+        rl[n] = a.tt_rloc[i];
+        pc[n] = a.pcol[i];
+    }
+    // Round B: the columns of those vertices, flux vectors, U* and <<U>> (a lane past the
+    // last layer reads that layer again)
+    double H0v[OB + HB + 1], etv[OB + HB + 1], hnv[OB + HB + 1][L], hzv[OB + HB + 1][L];
+#pragma unroll
+    for (int q = 0; q < OB + HB; ++q) {
+        const int64_t v = vs[q];
+        H0v[q] = a.H0[v];
+        etv[q] = a.eta_new[v];
+#pragma unroll
+        for (int l = 0; l < L; ++l) {
+            const int64_t i = v * K + min(8 * l + g, K - 1);
+            hnv[q][l] = a.hn[i];
+            hzv[q][l] = a.h0[i];
+        }
+    }
+    const d2v *S2 = reinterpret_cast<const d2v *>(S);
+    d2v se[EI];
+#pragma unroll
+    for (int n = 0; n < EI; ++n) se[n] = S2[pc[n]];
     d2v Ut[TPG][L];
     int64_t ge[TPG];
     int pk[TPG];
     double uax[TPG], uay[TPG];
 #pragma unroll
     for (int q = 0; q < TPG; ++q) {
-        const int2 rec = a.tt_le[le_off + min(grp + 32 * q, nel - 1)];
-        ge[q] = rec.x;
-        pk[q] = rec.y;
+        ge[q] = rec[q].x;
+        pk[q] = rec[q].y;
 #pragma unroll
-        for (int l = 0; l < L; ++l) {
-            const int k = 8 * l + g;
-            Ut[q][l] = k < K ? *reinterpret_cast<const d2v *>(a.Ustar + 2 * (ge[q] * K + k))
-                             : d2v{0.0, 0.0};
-        }
-        uax[q] = a.Uavg[2 * ge[q]];
-        uay[q] = a.Uavg[2 * ge[q] + 1];
-    }
-    const int32_t jb = a.row_ptr[v0];
-    int j0[TT_VPG], j1[TT_VPG];
-#pragma unroll
-    for (int q = 0; q < TT_VPG; ++q) {
-        const int lv = grp + 32 * q;
-        const int64_t v = v0 + min(lv, nvo - 1);
-        j0[q] = a.row_ptr[v];
-        j1[q] = lv < nvo ? a.row_ptr[v + 1] : j0[q];
+        for (int l = 0; l < L; ++l)
+            Ut[q][l] = *reinterpret_cast<const d2v *>(a.Ustar +
+                                                      2 * (ge[q] * K + min(8 * l + g, K - 1)));
     }
     // 1. vertex columns
     double dh[TT_VPG][L];
 #pragma unroll
-    for (int q = 0; q < TT_VPG; ++q) {
-        const int lv = grp + 32 * q;
+    for (int q = 0; q < TT_VPG; ++q)
 #pragma unroll
         for (int l = 0; l < L; ++l) dh[q][l] = 0.0;
-        if (lv < nvo) {
-            const int64_t v = v0 + lv;
-            const double sc = (a.H0[v] + a.eta_new[v]) / a.H0[v];
+    auto own_column = [&](int q, double sc, const double (&hn)[L], const double (&hz)[L]) {
+        const int lv = grp + 32 * q;
+        const int64_t v = v0 + lv;
 #pragma unroll
-            for (int l = 0; l < L; ++l) {
-                const int k = 8 * l + g;
-                if (k < K) {
-                    const double hn = a.hn[v * K + k];
-                    const double h = a.h0[v * K + k] * sc;
-                    a.hnew[v * K + k] = h;
-                    sP[lv * K + k] = hn + h;
-                    dh[q][l] = (h - hn) * inv_tau;
-                }
+        for (int l = 0; l < L; ++l) {
+            const int k = 8 * l + g;
+            if (lv < nvo && k < K) {
+                const double h = hz[l] * sc;
+                a.hnew[v * K + k] = h;
+                sP[lv * K + k] = hn[l] + h;
+                dh[q][l] = (h - hn[l]) * inv_tau;
+            }
+        }
+    };
+#pragma unroll
+    for (int q = 0; q < OB; ++q) own_column(q, (H0v[q] + etv[q]) / H0v[q], hnv[q], hzv[q]);
+#pragma unroll
+    for (int q = 0; q < HB; ++q) {
+        const int lv = nvo + grp + 32 * q;
+        const double sc = (H0v[OB + q] + etv[OB + q]) / H0v[OB + q];
+#pragma unroll
+        for (int l = 0; l < L; ++l) {
+            const int k = 8 * l + g;
+            if (lv < nvl && k < K) {
+                const double h = hzv[OB + q][l] * sc;
+                sP[lv * K + k] = hnv[OB + q][l] + h;
             }
         }
     }
-    for (int lv = nvo + grp; lv < nvl; lv += 32) {
+#pragma unroll
+    for (int n = 0; n < EI; ++n)
+        if (tid + 256 * n < nent) {
+            sL[tid + 256 * n] = rl[n];
+            sS[tid + 256 * n] = se[n];
+        }
+#pragma unroll
+    for (int q = 0; q < TPG; ++q) {   // (needed after the barrier alone)
+        uax[q] = a.Uavg[2 * ge[q]];
+        uay[q] = a.Uavg[2 * ge[q] + 1];
+    }
+    // the vertices beyond
+#pragma unroll
+    for (int q = OB; q < TT_VPG; ++q)
+        if (32 * q < nvo) {
+            const int64_t v = v0 + min(grp + 32 * q, nvo - 1);
+            double hn[L], hz[L];
+#pragma unroll
+            for (int l = 0; l < L; ++l) {
+                const int64_t i = v * K + min(8 * l + g, K - 1);
+                hn[l] = a.hn[i];
+                hz[l] = a.h0[i];
+            }
+            own_column(q, (a.H0[v] + a.eta_new[v]) / a.H0[v], hn, hz);
+        }
+    for (int lv = nvo + grp + 32 * HB; lv < nvl; lv += 32) {
         const int64_t v = a.tt_lv[lv_off + lv - nvo];
         const double sc = (a.H0[v] + a.eta_new[v]) / a.H0[v];
 #pragma unroll
@@ -390,11 +476,6 @@ __global__ void __launch_bounds__(256) k_trim_tile(TrimArgs a, const double *S) 
                 sP[lv * K + k] = a.hn[v * K + k] + h;
             }
         }
-    }
-    const d2v *S2 = reinterpret_cast<const d2v *>(S);
-    for (int i = tid; i < nent; i += 256) {
-        sL[i] = a.tt_rloc[jb + i];
-        sS[i] = S2[a.pcol[jb + i]];
     }
     __syncthreads();
     // 2. trim
@@ -408,8 +489,8 @@ __global__ void __launch_bounds__(256) k_trim_tile(TrimArgs a, const double *S) 
             const int k = 8 * l + g;
             hh[l] = k < K ? (sP[la * K + k] + sP[lb * K + k]) + sP[lc * K + k] : 0.0;
             hs += hh[l];
-            sx += Ut[q][l].x;
-            sy += Ut[q][l].y;
+            sx += k < K ? Ut[q][l].x : 0.0;
+            sy += k < K ? Ut[q][l].y : 0.0;
         }
         hs = grp_sum(hs);
         const double ex = grp_sum(sx) - uax[q];
@@ -423,11 +504,12 @@ __global__ void __launch_bounds__(256) k_trim_tile(TrimArgs a, const double *S) 
             d2v r;
             r.x = Ut[q][l].x - qh * ex;
             r.y = Ut[q][l].y - qh * ey;
-            Ut[q][l] = r;
+            Ut[q][l] = k < K ? r : d2v{0.0, 0.0};
             if (own && k < K) st_stream(a.U + 2 * (ge[q] * K + k), r);
         }
     }
     // 3. layer divergences of the own vertices, NB blocks of 8 layers at a time
+    if constexpr (L > 7) row_bounds();   // (its registers are all taken before)
     double div[TT_VPG][L];
 #pragma unroll
     for (int q = 0; q < TT_VPG; ++q)
@@ -445,7 +527,7 @@ __global__ void __launch_bounds__(256) k_trim_tile(TrimArgs a, const double *S) 
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < TT_VPG; ++q)
-            for (int jj = j0[q] - jb; jj < j1[q] - jb; ++jj) {
+            for (int jj = j0[q] - jb; jj < (grp + 32 * q < nvo ? j1[q] : j0[q]) - jb; ++jj) {
                 const d2v sv = sS[jj];
                 const d2v *F = sU + sL[jj] * 8 + g;
 #pragma unroll

@@ -396,12 +396,15 @@ bool build_trim_tiles(const HostMesh &m, int cap_e, int cap_o, int cap_v, TrimTi
         }
         for (int32_t j = m.row_ptr[v0]; j < m.row_ptr[v1]; ++j)
             out.rloc[j] = static_cast<uint16_t>(eloc[m.col[j] >> 2]);
-        const int32_t h[8] = {static_cast<int32_t>(v0), nvo, nvo + nh,
-                              static_cast<int32_t>(te.size()), neo, lv_off, le_off,
-                              m.row_ptr[v1] - m.row_ptr[v0]};
+        const int32_t h[8] = {static_cast<int32_t>(v0), nvo | (nvo + nh) << 16,
+                              static_cast<int32_t>(te.size()) | neo << 16, lv_off, le_off,
+                              m.row_ptr[v1] - m.row_ptr[v0], m.row_ptr[v0], 0};
         out.hdr.insert(out.hdr.end(), h, h + 8);
         v0 = v1;
     }
+    out.lv.push_back(0);   // read past the last tile's where it has none
+    out.le.push_back(0);
+    out.le.push_back(0);
     out.ntiles = t;
     return true;
 }

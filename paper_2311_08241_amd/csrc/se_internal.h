@@ -42,10 +42,11 @@ se_status build_visc_tables(const HostMesh &m, std::vector<int32_t> &nb4,
 
 // Tiles of the trim/z* consumer: runs of consecutive vertices, each with every triangle
 // of its vertices' CSR rows (at most cap_e), the vertices of those triangles (at most
-// cap_v) and at most cap_o vertices of its own.  hdr [ntiles][8]: first vertex v0, own
-// vertices nvo, local vertices nvl (own first, then the others ascending: lv), local
-// triangles nel, owned triangles neo (smallest vertex in the run; the first neo local
-// triangles, ascending), offset into lv, offset into le, CSR entries of the run's rows.
+// cap_v) and at most cap_o vertices of its own.  hdr [ntiles][8]: first vertex v0; own
+// vertices nvo | local vertices nvl << 16 (own first, then the others ascending: lv); local
+// triangles nel | owned triangles neo << 16 (smallest vertex in the run; the first neo local
+// triangles, ascending); offset into lv; offset into le; CSR entries of the run's rows; the
+// first of them; 0.  lv and le end in a spare entry.
 // le [2 per local triangle]: global id, local vertices a | b << 10 | c << 20.  rloc [3 ne]
 // (CSR order): local index of the entry's triangle in the tile owning the row.  Returns
 // false when one vertex's row alone exceeds a capacity.

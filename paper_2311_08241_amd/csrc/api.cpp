@@ -793,10 +793,13 @@ se_status mesh_plan(se_mesh *m, int cl, bool may_alloc, hipStream_t s, DevTiles 
     std::unique_ptr<DevTiles> p;
     bool any_ok = false;
     auto cand = default_plans(cl, m->h.nv);
-    if ((cl & ~1) == CL_ADJ) {   // none fits: the forward plans are asked
+    if ((cl & ~1) == CL_ADJ) {   // none fits: the forward plans are asked, now and later
+        if (m->no_adj[cl & 1]) return SE_OK;
         if (make_default(m, cl, cand, p, nullptr) == SE_OK) {
             m->dflt[cl] = std::move(p);
             *out = m->dflt[cl].get();
+        } else {
+            m->no_adj[cl & 1] = true;
         }
         return SE_OK;
     }
@@ -990,6 +993,7 @@ se_status se_set_plan(void *obj, int32_t kind, int32_t tile, int32_t k_fused, in
     {
         std::lock_guard<std::mutex> lk(m->plan_mu);
         for (auto &d : m->dflt) d.reset();
+        m->no_adj[0] = m->no_adj[1] = false;
     }
     m->plan = std::move(p);
     m->plan_T = tile;

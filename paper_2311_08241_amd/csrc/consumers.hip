@@ -663,12 +663,12 @@ __global__ void __launch_bounds__(256) k_forcing(ForcingArgs a) {
     if (a.Cd > 0.0) ub = *reinterpret_cast<const double2 *>(a.u + (base + last) * 2);
     double sx = 0.0, sy = 0.0;
     if constexpr (NA > 0) {
-        for (int k0 = j; k0 < K; k0 += FG * NB) {
-            if (k0 - j > last) break;   // the whole group
+        // unsigned: no overflow at the largest K
+        for (unsigned k0 = j; k0 - j <= static_cast<unsigned>(last); k0 += FG * NB) {
             d2v v[NB][NA];
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                const int64_t i = (base + min(k0 + FG * b, last)) * 2;
+                const int64_t i = (base + min(k0 + FG * b, static_cast<unsigned>(last))) * 2;
 #pragma unroll
                 for (int q = 0; q < NA; ++q) v[b][q] = ld_stream(a.col[q] + i);
             }
@@ -680,7 +680,7 @@ __global__ void __launch_bounds__(256) k_forcing(ForcingArgs a) {
                     lx += v[b][q].x;
                     ly += v[b][q].y;
                 }
-                if (k0 + FG * b <= last) {
+                if (k0 + FG * b <= static_cast<unsigned>(last)) {
                     sx += lx;
                     sy += ly;
                 }
@@ -724,7 +724,7 @@ hipError_t launch_visc(bool f32, const ViscArgs &a, hipStream_t s) {
 }
 
 template <int NA> void launch_forcing_n(const ForcingArgs &a, unsigned g, hipStream_t s) {
-    switch (NA ? min((a.K + FG - 1) / FG, 6) : 1) {
+    switch (NA ? (min(a.K, 6 * FG) + FG - 1) / FG : 1) {
         case 1: hipLaunchKernelGGL((k_forcing<NA, 1>), dim3(g), dim3(256), 0, s, a); break;
         case 2: hipLaunchKernelGGL((k_forcing<NA, 2>), dim3(g), dim3(256), 0, s, a); break;
         case 3: hipLaunchKernelGGL((k_forcing<NA, 3>), dim3(g), dim3(256), 0, s, a); break;

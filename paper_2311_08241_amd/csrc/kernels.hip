@@ -40,26 +40,51 @@ template <typename T> __device__ __forceinline__ T copt(const StepC &c);
 template <> __device__ __forceinline__ double copt<double>(const StepC &c) { return c.opt; }
 template <> __device__ __forceinline__ float copt<float>(const StepC &c) { return c.opt_f; }
 
+// Depth constant of a triangle (FP32: the mean H0, with eta_ref unless H is linear, eta the
+// deviation from eta_ref; FP64: the sum of the three H0) and its depth H = mean(H0 + eta)
+// (mean H0 with linear_h).  FP64 adds the sum of the elevations, formed in the same order,
+// before the division by three: a triangle whose elevations cancel its depths has H = 0
+// exactly and is reported dry, where a mean depth plus a third of the elevations leaves a
+// rounding (6e-16 m at 10 m).  One multiplication more than a fused one, in the registers
+// of one number; the three depths apart would take 130 VGPRs at three triangles per thread
+// instead of 126, one 512-thread tile per CU instead of two.
+template <typename T> struct TriDepth {
+    T h;
+};
+template <typename T>
+__device__ __forceinline__ TriDepth<T> tri_depth(T ha, T hb, T hc, bool linear_h, const StepC &c) {
+    if constexpr (sizeof(T) == 4)
+        return {(ha + hb + hc) * (1.0f / 3.0f) + (linear_h ? 0.0f : c.eta_ref_f)};
+    else
+        return {ha + hb + hc};
+}
+template <typename T>
+__device__ __forceinline__ T tri_height(TriDepth<T> d, T ea, T eb, T ec, bool linear_h) {
+    if constexpr (sizeof(T) == 4)
+        return linear_h ? d.h : __builtin_fmaf(ea + eb + ec, 1.0f / 3.0f, d.h);
+    else
+        return (linear_h ? d.h : d.h + (ea + eb + ec)) * (1.0 / 3.0);
+}
+
 // Triangle update, FP64 and FP32, with per-triangle constants of the call: a = f dt/2
-// (al), 1/(1 + a^2) (rk), dt R (dRx, dRy), -A_e (mAe), mean H0 (FP32: + eta_ref unless H is
-// linear) (rH); gd = g dt; ea..ec: eta at the vertices (FP64: absolute; FP32: deviation
-// from eta_ref).  Returns U' and the three sub-cell fluxes; dry is set when the triangle's
+// (al), 1/(1 + a^2) (rk), dt R (dRx, dRy), -A_e (mAe), the depth constant (d); gd = g dt;
+// ea..ec: eta at the vertices (FP64: absolute; FP32: deviation from eta_ref).  Returns U' and the three sub-cell fluxes; dry is set when the triangle's
 // total depth is not positive.  The Crank-Nicolson step is evaluated as the increment
 //   U' = U + C (q - 2 a J U),  C = (I + aJ)^-1,  q = dt (R - g H grad eta),
 // algebraically equal to C [(I - aJ) U + q]; the rounded rotation coefficients then perturb
 // only the small increment instead of scaling U by 1 + O(eps) every substep, which would
 // bias its amplitude over many substeps (visible in FP32).  Products that feed sums are
 // fused multiply-adds; the fluxes of vertices b and c are formed and a's is minus their
-// sum (the three vectors sum to zero).  Both precisions evaluate the same 31 operations;
-// the FP64 form in the order of the CPU definition took 60 FP64 instructions, most of a
-// small tile's substep (2,048 vertices 88.7 -> 81.7 us per call, 61,897 182 -> 167, 2.2M
-// 4.16 -> 4.10 ms).  Against an 80-bit evaluation the FP64 transports of 30 to 80 substeps
+// sum (the three vectors sum to zero).  Both precisions evaluate the same 31 operations
+// (FP64 one more in H); the FP64 form in the order of the CPU definition took 60 FP64
+// instructions, most of a small tile's substep (2,048 vertices 88.7 -> 81.7 us per call,
+// 61,897 182 -> 167, 2.2M 4.16 -> 4.10 ms).  Against an 80-bit evaluation the FP64 transports of 30 to 80 substeps
 // are 3e-16 to 5e-16 off in the 2-norm, 1.7e-15 to 4.7e-15 before.
 template <typename T>
-__device__ __forceinline__ void tri_update(T ea, T eb, T ec, T rH, T gbx, T gby, T gcx, T gcy,
-                                           T mAe, T ux, T uy, T dRx, T dRy, T al, T rk, T gd, T th,
-                                           bool linear_h, T &Unx, T &Uny, T &pa, T &pb, T &pc,
-                                           bool &dry) {
+__device__ __forceinline__ void tri_update(T ea, T eb, T ec, TriDepth<T> d, T gbx, T gby, T gcx,
+                                           T gcy, T mAe, T ux, T uy, T dRx, T dRy, T al, T rk,
+                                           T gd, T th, bool linear_h, T &Unx, T &Uny, T &pa,
+                                           T &pb, T &pc, bool &dry) {
     // fused multiply-adds (one rounding each) where a product feeds a sum
     auto fma = [](T x, T y, T z) -> T {
         if constexpr (sizeof(T) == 4) return __builtin_fmaf(x, y, z);
@@ -68,7 +93,7 @@ __device__ __forceinline__ void tri_update(T ea, T eb, T ec, T rH, T gbx, T gby,
     const T db = eb - ea, dc = ec - ea;
     const T gx = fma(db, gbx, dc * gcx);
     const T gy = fma(db, gby, dc * gcy);
-    const T He = linear_h ? rH : fma(ea + eb + ec, T(1) / T(3), rH);
+    const T He = tri_height<T>(d, ea, eb, ec, linear_h);
     dry = !(He > T(0));
     const T gHe = gd * He;
     const T al2 = T(2) * al;
@@ -98,14 +123,6 @@ __device__ __forceinline__ double vtx_update(double eta, double acc, double rav,
 template <typename T> __device__ __forceinline__ void tri_consts(T f, T dts, T &al, T &rk) {
     al = T(0.5) * f * dts;
     rk = T(1) / (T(1) + al * al);
-}
-
-// Mean depth constant of a triangle (FP32: with eta_ref unless H is linear).
-template <typename T>
-__device__ __forceinline__ T tri_mean_h(T ha, T hb, T hc, bool linear_h, const StepC &c) {
-    const T h = (ha + hb + hc) * (T(1) / T(3));
-    if constexpr (sizeof(T) == 4) return h + (linear_h ? 0.0f : c.eta_ref_f);
-    else return h;
 }
 
 // Non-temporal accesses of the tile kernels.  A tile's own triangle records, geometry
@@ -233,7 +250,7 @@ __device__ __forceinline__ void plain_tri_at(const PlainArgs &a, int64_t e) {
     const T dts = cdts<T>(c);
     T al, rk;
     tri_consts<T>(fc, dts, al, rk);
-    tri_update<T>(eta[va], eta[vb], eta[vc], tri_mean_h<T>(H0[va], H0[vb], H0[vc], linear_h, c),
+    tri_update<T>(eta[va], eta[vb], eta[vc], tri_depth<T>(H0[va], H0[vb], H0[vc], linear_h, c),
                   geom[e], geom[a.ne + e], geom[2 * a.ne + e], geom[3 * a.ne + e],
                   -geom[4 * a.ne + e], u.x, u.y, dts * r.x, dts * r.y, al, rk, cg<T>(c) * dts,
                   cth<T>(c), linear_h, Unx, Uny, pa, pb, pc, dry);
@@ -1015,17 +1032,17 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
         }
         if constexpr (F32 || !SM) g4[r] = -g4[r];
     }
-    // the mean depth constant in registers, except in FP64 beyond two triangles per thread
+    // the depth constant in registers, except in FP64 beyond two triangles per thread
     // (formed from LDS at every substep, the same operations)
     constexpr bool HM = F32 || (!SM && EPT <= 2);
-    T rH[HM ? EPT : 1];
+    TriDepth<T> rH[HM ? EPT : 1];
     if constexpr (HM) {
 #pragma unroll
         for (int r = 0; r < EPT; ++r) {
             const int le = tid + r * BLOCK;
             if (le < ne_load)
-                rH[r] = tri_mean_h<T>(sH[t0[r] & 0xffffu], sH[t0[r] >> 16], sH[t1[r] & 0xffffu],
-                                      linear_h, c);
+                rH[r] = tri_depth<T>(sH[t0[r] & 0xffffu], sH[t0[r] >> 16], sH[t1[r] & 0xffffu],
+                                     linear_h, c);
         }
     }
 
@@ -1129,7 +1146,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
                         bool dry;
                         const T eAa = sEA[ia], eAb = sEA[ib], eAc = sEA[ic];
                         if constexpr (F32)
-                            sesm_u_f32(linear_h, eAa, eAb, eAc, rH[r], g0[r], g1[r], g2[r], g3[r],
+                            sesm_u_f32(linear_h, eAa, eAb, eAc, rH[r].h, g0[r], g1[r], g2[r], g3[r],
                                        rf[r], rRx[r], rRy[r], gd, Px, Py, aUx[r], aUy[r], Unx,
                                        Uny, dry);
                         else
@@ -1200,7 +1217,8 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
                     const T ea = (F32 && FB) ? hE[(F32 && FB) ? 3 * r : 0] : sEta[ia];
                     const T eb = (F32 && FB) ? hE[(F32 && FB) ? 3 * r + 1 : 0] : sEta[ib];
                     const T ec = (F32 && FB) ? hE[(F32 && FB) ? 3 * r + 2 : 0] : sEta[ic];
-                    const T hm = HM ? rH[HM ? r : 0] : tri_mean_h<T>(sH[ia], sH[ib], sH[ic], linear_h, c);
+                    const TriDepth<T> hm =
+                        HM ? rH[HM ? r : 0] : tri_depth<T>(sH[ia], sH[ib], sH[ic], linear_h, c);
                     tri_update<T>(ea, eb, ec, hm, g0[r], g1[r], g2[r], g3[r], g4[r], rUx[r],
                                   rUy[r], rx, ry, rf[r], rk[r], gd, th, linear_h, Unx, Uny, pa,
                                   pb, pc, dry);
@@ -1402,7 +1420,7 @@ __global__ void __launch_bounds__(BLOCK) k_tile(TileArgs a) {
 // ---------------------------------------------------------------------------
 // Reverse of one triangle's substep, shared by the per-substep and the tile kernels (equal
 // bit for bit).  wa..wc: dt_s lambda_eta / A at the vertices; ea..ec the forward elevations;
-// rH mean H0 (FP32: + eta_ref unless H is linear); mAe = -A_e; gd = g dt_s.  Updates the
+// d the depth constant; mAe = -A_e; gd = g dt_s.  Updates the
 // adjoint transport (lx, ly), adds to the R gradient, returns the three slot terms and
 // lambda_H / 3.  The three gradients of a triangle sum to zero, so lambda_F and the slot
 // terms are formed from those of b and c alone; products that feed sums are fused
@@ -1410,8 +1428,8 @@ __global__ void __launch_bounds__(BLOCK) k_tile(TileArgs a) {
 // adjoint to rounding).  43 operations; 86 when every vector was formed and every product
 // rounded.
 template <typename T>
-__device__ __forceinline__ void adj_update(T wa, T wb, T wc, T ea, T eb, T ec, T rH, T gbx, T gby,
-                                           T gcx, T gcy, T mAe, T al, T rk, T gd, T dts, T th, T opt,
+__device__ __forceinline__ void adj_update(T wa, T wb, T wc, T ea, T eb, T ec, TriDepth<T> d, T gbx,
+                                           T gby, T gcx, T gcy, T mAe, T al, T rk, T gd, T dts, T th, T opt,
                                            bool linear_h, T &lx, T &ly, T &grx, T &gry, T &pa,
                                            T &pb, T &pc, T &chi) {
     auto fma = [](T x, T y, T z) -> T {
@@ -1428,7 +1446,7 @@ __device__ __forceinline__ void adj_update(T wa, T wb, T wc, T ea, T eb, T ec, T
     const T db = eb - ea, dc = ec - ea;
     const T gx = fma(db, gbx, dc * gcx);
     const T gy = fma(db, gby, dc * gcy);
-    const T He = linear_h ? rH : fma(ea + eb + ec, third, rH);
+    const T He = tri_height<T>(d, ea, eb, ec, linear_h);
     // U' = C r with C = (I + aJ)^-1:  lambda_r = C^T lambda_U'
     const T lrx = fma(-al, lUny, lUnx) * rk;
     const T lry = fma(al, lUnx, lUny) * rk;
@@ -1472,7 +1490,7 @@ __device__ __forceinline__ void adj_tri_at(const AdjArgs &a, int64_t e) {
     T *psi = static_cast<T *>(a.psi) + 4 * e;
     adj_update<T>(dts * le[v0] * (T(1) / Av[v0]), dts * le[v1] * (T(1) / Av[v1]),
                   dts * le[v2] * (T(1) / Av[v2]), eta[v0], eta[v1], eta[v2],
-                  tri_mean_h<T>(H0[v0], H0[v1], H0[v2], linear_h, c), geom[e], geom[a.ne + e],
+                  tri_depth<T>(H0[v0], H0[v1], H0[v2], linear_h, c), geom[e], geom[a.ne + e],
                   geom[2 * a.ne + e], geom[3 * a.ne + e], -geom[4 * a.ne + e], al, rk,
                   cg<T>(c) * dts, dts, th, opt, linear_h, lu.x, lu.y, gr.x, gr.y, psi[0], psi[1],
                   psi[2], psi[3]);
@@ -1822,7 +1840,7 @@ __device__ __forceinline__ void adj_tile_body(const AdjTileArgs &a, int b, int G
                 gqy = gry[r < OS ? r : 0];
             }
             adj_update<T>(dts * sLe[ia] * sAv[ia], dts * sLe[ib] * sAv[ib], dts * sLe[ic] * sAv[ic], em[ia], em[ib],
-                          em[ic], tri_mean_h<T>(sH[ia], sH[ib], sH[ic], linear_h, c), g0[r], g1[r],
+                          em[ic], tri_depth<T>(sH[ia], sH[ib], sH[ic], linear_h, c), g0[r], g1[r],
                           g2[r], g3[r], g4[r], al[r], den[r], gd, dts, th, opt, linear_h, lux, luy,
                           gqx, gqy, qa, qb, qc, chi);
             if (r < OS) {

@@ -607,7 +607,8 @@ se_status check_device(const se_mesh *m) {
 }
 
 // Forms of the subcycle that a default plan is chosen for.
-enum : int { CL_FB = 0, CL_SESM = 2, CL_VISC = 4, CL_ADJ = 6, CL_ANY = 8 };   // + 1: FP32; ANY: every form
+// + 1: FP32; ANY: every form, ANY + 1: every form but the viscous one
+enum : int { CL_FB = 0, CL_SESM = 2, CL_VISC = 4, CL_ADJ = 6, CL_ANY = 8 };
 
 bool plan_fits(int cl, const HostTiles &ht, const se_plan_stats_t &st, int32_t K, int32_t block) {
     const bool f32 = cl & 1;
@@ -621,8 +622,18 @@ bool plan_fits(int cl, const HostTiles &ht, const se_plan_stats_t &st, int32_t K
         case CL_ADJ:
             return (f32 ? st.ok_f32 : st.ok_f64) &&
                    adj_fits(f32, ht.max_nv, ht.max_nvu, ht.max_cs, ht.T, K, block, st.tri_per_thread);
-        default: return st.ok_f32 && st.ok_f64 && st.ok_sesm_f32 && st.ok_sesm_f64;
+        default:
+            return st.ok_f32 && st.ok_f64 && st.ok_sesm_f32 && st.ok_sesm_f64 &&
+                   (cl != CL_ANY || (plan_fits(CL_VISC, ht, st, K, block) &&
+                                     plan_fits(CL_VISC + 1, ht, st, K, block)));
     }
+}
+
+// The viscous form of this precision runs on a plan.
+bool visc_fits(const DevTiles &P, bool f32) {
+    return P.ok(f32, false) && P.K >= 2 &&
+           visc_lds(P.lds(f32, false), f32, P.max_ne) <= 160 * 1024 &&
+           visc_regs_ok(f32, P.block, P.ept);
 }
 
 // A candidate of a form's default plan: at most ept triangles per thread, and ntiles
@@ -735,8 +746,9 @@ std::vector<PlanCand> default_plans(int cl, int64_t nv) {
     return c;
 }
 
-// Plans that run every form without spills, largest tiles first: the default before a
-// form's own, and the one that a call that may not allocate falls back on.
+// Plans that run every form without spills, largest tiles first: the one that a call that
+// may not allocate falls back on (a mesh none of them runs the viscous form on, such as one
+// of long rows, takes the first that runs the others).
 const std::vector<PlanCand> kAnyPlans = {
     {1024, 4, 512, 8, 0}, {512, 4, 512, 8, 0}, {512, 4, 256, 8, 0}, {512, 2, 256, 8, 0},
     {256, 4, 256, 8, 0},  {256, 2, 256, 8, 0}, {128, 2, 256, 8, 0}, {64, 1, 256, 8, 0}};
@@ -809,7 +821,8 @@ se_status mesh_plan(se_mesh *m, int cl, bool may_alloc, hipStream_t s, DevTiles 
         // a form whose own plan runs every form needs no second one
         if (!any_ok) {
             std::unique_ptr<DevTiles> a;
-            SE_TRY(make_default(m, CL_ANY, kAnyPlans, a, nullptr));
+            if (make_default(m, CL_ANY, kAnyPlans, a, nullptr) != SE_OK)
+                SE_TRY(make_default(m, CL_ANY + 1, kAnyPlans, a, nullptr));
             m->dflt[CL_ANY] = std::move(a);
         }
         m->plan_T = p->T;
@@ -1169,8 +1182,7 @@ se_status sesub::subcycle_tile(se_mesh *m, const se_params *p, se_state *st,
     if (visc) {
         // two rings per substep
         lds = visc_lds(lds, f32, P.max_ne);
-        const bool regs_ok = visc_regs_ok(f32, P.block, P.ept);
-        if (P.K < 2 || lds > 160 * 1024 || !regs_ok) {
+        if (!visc_fits(P, f32)) {
             set_error("se_subcycle: with the viscous term the plan needs k_fused >= 2, " +
                       std::to_string(lds) + " bytes of LDS within 160 KiB and at most " +
                       "3 / 1 (1024 threads) or 6 / 4 (512 threads) triangles per thread "
@@ -1182,8 +1194,20 @@ se_status sesub::subcycle_tile(se_mesh *m, const se_params *p, se_state *st,
                       "built yet (one se_subcycle call with the viscous term builds them)");
             return SE_ERR_ARG;
         }
+        const bool built = P.vnb.p != nullptr;
         SE_TRY(ensure_visc(m));
         SE_TRY(ensure_tile_visc(m, P));
+        if (!built && !m->plan) {
+            // the tables of the plan that a later call of the other precision runs on when it
+            // may not allocate (should they not fit, it is that call that reports it)
+            DevTiles *any;
+            {
+                std::lock_guard<std::mutex> lk(m->plan_mu);
+                any = m->dflt[CL_ANY].get();
+            }
+            if (any && any != &P && (visc_fits(*any, false) || visc_fits(*any, true)))
+                (void)ensure_tile_visc(m, *any);
+        }
     }
     const hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t nv = m->h.nv, ne = m->h.ne;

@@ -26,6 +26,8 @@ enum : int32_t { KF_LINEAR_H = 1, KF_TRACK_VOLUME = 4 };
 // unused entries zero (odd, so that the rows of consecutive vertices fall in
 // distinct LDS banks).
 constexpr int kEllWidth = 7;
+// Most local vertices of a tile with such rows (a record's 13 bits).
+constexpr int kEllMaxVtx = 8192;
 
 // Most rings (inner substeps) of one launch.
 constexpr int kMaxFused = 8;

@@ -661,7 +661,8 @@ se_status build_tiles(const std::vector<const HostMesh *> &members,
     out = HostTiles();
     out.T = T;
     out.K = K;
-    // fixed-width rows when no vertex of any member has more than kEllWidth triangles
+    // fixed-width rows when no vertex of any member has more than kEllWidth triangles (and no
+    // tile more than kEllMaxVtx vertices, below)
     int32_t max_deg = 0;
     for (const HostMesh *m : members)
         for (int64_t v = 0; v < m->nv; ++v)
@@ -680,6 +681,15 @@ se_status build_tiles(const std::vector<const HostMesh *> &members,
     }
     se_status rc = build_tiles_pass(members, voff, eoff, vstart, efirst, K, out.ell, out);
     if (rc != SE_OK) return rc;
+    // a record of fixed-width rows holds a local vertex in 13 bits: a tile of more (thousands
+    // of triangles that share few vertices) takes compact rows, whose records hold 16
+    if (out.ell && out.max_nv > kEllMaxVtx) {
+        out = HostTiles();
+        out.T = T;
+        out.K = K;
+        rc = build_tiles_pass(members, voff, eoff, vstart, efirst, K, false, out);
+        if (rc != SE_OK) return rc;
+    }
     // split_cap > 0: halve every tile with more local triangles than split_cap (its
     // halves again, up to four times), keeping the tiles in vertex order
     for (int round = 0; split_cap > 0 && round < 4 && out.max_ne > split_cap; ++round) {

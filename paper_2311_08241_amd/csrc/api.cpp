@@ -802,36 +802,52 @@ se_status mesh_plan(se_mesh *m, int cl, bool may_alloc, hipStream_t s, DevTiles 
         *out = any;   // null: no plan yet
         return SE_OK;
     }
+    if (m->no_own[cl]) {
+        *out = (cl & ~1) == CL_ADJ ? nullptr : any;
+        return SE_OK;
+    }
     std::unique_ptr<DevTiles> p;
     bool any_ok = false;
     auto cand = default_plans(cl, m->h.nv);
     if ((cl & ~1) == CL_ADJ) {   // none fits: the forward plans are asked, now and later
-        if (m->no_adj[cl & 1]) return SE_OK;
         if (make_default(m, cl, cand, p, nullptr) == SE_OK) {
             m->dflt[cl] = std::move(p);
             *out = m->dflt[cl].get();
         } else {
-            m->no_adj[cl & 1] = true;
+            m->no_own[cl] = true;
         }
         return SE_OK;
     }
     cand.insert(cand.end(), kAnyPlans.begin(), kAnyPlans.end());
-    SE_TRY(make_default(m, cl, cand, p, &any_ok));
-    if (!any) {
-        // a form whose own plan runs every form needs no second one
-        if (!any_ok) {
-            std::unique_ptr<DevTiles> a;
-            if (make_default(m, CL_ANY, kAnyPlans, a, nullptr) != SE_OK)
-                SE_TRY(make_default(m, CL_ANY + 1, kAnyPlans, a, nullptr));
-            m->dflt[CL_ANY] = std::move(a);
+    const se_status own = make_default(m, cl, cand, p, &any_ok);
+    if (!any && (own != SE_OK || !any_ok)) {
+        // (a form whose own plan runs every form needs no second one)
+        std::unique_ptr<DevTiles> a;
+        auto make_any = [&] {
+            return make_default(m, CL_ANY, kAnyPlans, a, nullptr) == SE_OK
+                       ? SE_OK : make_default(m, CL_ANY + 1, kAnyPlans, a, nullptr);
+        };
+        if (make_any() != SE_OK) {   // no memory for both
+            if (!p) return own;
+            p.reset();
+            SE_TRY(make_any());
         }
-        m->plan_T = p->T;
-        m->plan_K = p->K;
-        m->plan_block = p->block;
+        m->dflt[CL_ANY] = std::move(a);
     }
-    m->dflt[cl] = std::move(p);
-    if (!m->dflt[CL_ANY]) m->dflt[CL_ANY] = m->dflt[cl];
-    *out = m->dflt[cl].get();
+    const DevTiles *first = p ? p.get() : m->dflt[CL_ANY].get();
+    if (!any) {
+        m->plan_T = first->T;
+        m->plan_K = first->K;
+        m->plan_block = first->block;
+    }
+    if (p) {
+        m->dflt[cl] = std::move(p);
+        if (!m->dflt[CL_ANY]) m->dflt[CL_ANY] = m->dflt[cl];
+        *out = m->dflt[cl].get();
+    } else {   // no memory for a plan of its own: the one for every form, now and later
+        m->no_own[cl] = true;
+        *out = m->dflt[CL_ANY].get();
+    }
     return SE_OK;
 }
 
@@ -1006,7 +1022,7 @@ se_status se_set_plan(void *obj, int32_t kind, int32_t tile, int32_t k_fused, in
     {
         std::lock_guard<std::mutex> lk(m->plan_mu);
         for (auto &d : m->dflt) d.reset();
-        m->no_adj[0] = m->no_adj[1] = false;
+        for (bool &b : m->no_own) b = false;
     }
     m->plan = std::move(p);
     m->plan_T = tile;

@@ -182,7 +182,8 @@ struct se_mesh {
     // (forward-backward, AB3-AM4, viscous, the adjoint; FP64, FP32), and one that runs every form
     // (one of the others where that runs them all)
     std::shared_ptr<sesub::DevTiles> dflt[9];
-    bool no_adj[2] = {false, false};            // no default of the adjoint fits (FP64, FP32)
-    std::mutex plan_mu;                         // guards dflt and no_adj
+    bool no_own[8] = {};                        // a form without a default of its own: none fits
+                                                // (the adjoint), or no device memory for one
+    std::mutex plan_mu;                         // guards dflt and no_own
     int32_t plan_T = 1024, plan_K = 4, plan_block = 256;
 };

@@ -1996,31 +1996,36 @@ struct se_batch {
     std::vector<int64_t> voff, eoff;
     int64_t nv = 0, ne = 0;
     std::vector<double> atot;            // per member total area
-    sesub::DevBuf Av64, Av32, faults, table, lists;
-    std::vector<sesub::StepC> table_host;
-    // one-launch epilogue of a call: volume rows of every member, final states that
-    // ended in the workspace copied back (per configuration, host copies to compare)
-    sesub::DevBuf voltab, cpytab;
-    std::vector<sesub::VolMember> voltab_host;
-    std::vector<sesub::CopyRange> cpytab_host;
-    std::vector<int32_t> list_off;       // per launch offset into lists (size nlaunch + 1)
-    std::unique_ptr<sesub::DevTiles> plan;
+    sesub::DevBuf Av64, Av32, faults;
     int32_t plan_T = 768, plan_K = 4, plan_block = 512;
-    std::vector<int32_t> mtiles, mtile_first;
     struct Graph {
         std::vector<uint64_t> key;
         hipGraph_t g = nullptr;
         hipGraphExec_t x = nullptr;
     };
-    std::vector<Graph> graphs;
-    void drop_graphs() {
-        for (auto &gr : graphs) {
-            if (gr.x) (void)hipGraphExecDestroy(gr.x);
-            if (gr.g) (void)hipGraphDestroy(gr.g);
+    // What the calls of one precision run on: the plan (the caller's, one for both precisions,
+    // or a default of that precision) and what follows from it and the last configuration
+    struct Exec {
+        std::shared_ptr<sesub::DevTiles> plan;
+        std::vector<int32_t> mtiles, mtile_first;   // tiles per member, the first of them
+        sesub::DevBuf table, lists;
+        std::vector<sesub::StepC> table_host;
+        std::vector<int32_t> list_off;   // per launch offset into lists (size nlaunch + 1)
+        // one-launch epilogue of a call: volume rows of every member, final states that
+        // ended in the workspace copied back (per configuration, host copies to compare)
+        sesub::DevBuf voltab, cpytab;
+        std::vector<sesub::VolMember> voltab_host;
+        std::vector<sesub::CopyRange> cpytab_host;
+        std::vector<Graph> graphs;
+        void drop_graphs() {
+            for (auto &gr : graphs) {
+                if (gr.x) (void)hipGraphExecDestroy(gr.x);
+                if (gr.g) (void)hipGraphDestroy(gr.g);
+            }
+            graphs.clear();
         }
-        graphs.clear();
-    }
-    ~se_batch() { drop_graphs(); }
+        ~Exec() { drop_graphs(); }
+    } exec[2];                           // FP64, FP32
 };
 
 namespace sesub {
@@ -2032,24 +2037,18 @@ std::vector<const HostMesh *> batch_members(const se_batch *b) {
     return v;
 }
 
-se_status batch_install_plan(se_batch *b, int32_t T, int32_t K, int32_t block) {
-    std::unique_ptr<DevTiles> p;
-    SE_TRY(make_plan(batch_members(b), b->voff, b->eoff, T, K, block, p));
+void batch_use_plan(se_batch *b, se_batch::Exec &x, const std::shared_ptr<DevTiles> &p) {
     const size_t n = b->h.size();
-    b->mtiles.assign(n, 0);
-    b->mtile_first.assign(n, -1);
+    x.mtiles.assign(n, 0);
+    x.mtile_first.assign(n, -1);
     for (size_t t = 0; t < p->hdr_host.size(); ++t) {
         const int mb = p->hdr_host[t].member;
-        if (b->mtile_first[mb] < 0) b->mtile_first[mb] = static_cast<int32_t>(t);
-        b->mtiles[mb]++;
+        if (x.mtile_first[mb] < 0) x.mtile_first[mb] = static_cast<int32_t>(t);
+        x.mtiles[mb]++;
     }
-    b->plan = std::move(p);
-    b->plan_T = T;
-    b->plan_K = K;
-    b->plan_block = block;
-    b->table_host.clear();   // forces a new schedule
-    b->drop_graphs();
-    return SE_OK;
+    x.plan = p;
+    x.table_host.clear();   // forces a new schedule
+    x.drop_graphs();
 }
 
 // Default plan of a batch, chosen at its first call from the vertices of all members and
@@ -2058,8 +2057,22 @@ se_status batch_install_plan(se_batch *b, int32_t T, int32_t K, int32_t block) {
 // of 3,000 to 40,000 vertices (513,187 in all) FP32: 512,2,512 1045, 352,5,512 722 us per
 // call cold; FP64 1927, 256,4,512 1234; eight of 2,000 to 8,000 (36,883) 256,4,512 236 and
 // 283, 128,8,512 196 and 233.
-se_status batch_ensure_plan(se_batch *b, bool f32) {
-    if (b->plan) return SE_OK;
+//
+// One default per precision, so that a call runs on the same plan whichever precision came
+// first (24 basins FP64 after FP32: 1,324 us on the FP32 plan, 1,054 on its own).  Where no
+// plan may be made (a stream under capture) or none finds memory, the other precision's
+// stands in: a default runs in both.
+se_status batch_exec(se_batch *b, bool f32, hipStream_t s, se_batch::Exec **out) {
+    se_batch::Exec &x = b->exec[f32 ? 1 : 0], &other = b->exec[f32 ? 0 : 1];
+    *out = &x;
+    if (x.plan) return SE_OK;
+    if (other.plan && s) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+            *out = &other;
+            return SE_OK;
+        }
+    }
     std::vector<PlanCand> cand;
     if (b->nv <= 75000) {
         const int32_t T = std::max<int32_t>(64, static_cast<int32_t>((b->nv + 287) / 288 + 7) / 8 * 8);
@@ -2083,7 +2096,25 @@ se_status batch_ensure_plan(se_batch *b, bool f32) {
         if (plan_host(batch_members(b), b->voff, b->eoff, c.T, c.K, c.block, ht, st) != SE_OK)
             continue;
         if (!st.ok_f32 || !st.ok_f64 || st.tri_per_thread > c.ept) continue;
-        return batch_install_plan(b, c.T, c.K, c.block);
+        if (other.plan && other.plan->T == c.T && other.plan->K == c.K && other.plan->block == c.block) {
+            batch_use_plan(b, x, other.plan);
+            return SE_OK;
+        }
+        std::unique_ptr<DevTiles> p;
+        const se_status rc = upload_plan(batch_members(b), b->voff, b->eoff, c.T, c.K, c.block, ht, st, p);
+        if (rc == SE_OK) {
+            batch_use_plan(b, x, std::move(p));
+            if (!other.plan) {
+                b->plan_T = c.T;
+                b->plan_K = c.K;
+                b->plan_block = c.block;
+            }
+        } else if (other.plan) {
+            batch_use_plan(b, x, other.plan);
+        } else {
+            return rc;
+        }
+        return SE_OK;
     }
     set_error("no default plan fits this batch");
     return SE_ERR_ARG;
@@ -2237,9 +2268,10 @@ se_status se_subcycle_batched(se_batch *b, const se_params *p, se_state *st, con
         return SE_ERR_ARG;
     }
     DeviceGuard dg(b->device);
-    SE_TRY(batch_ensure_plan(b, p->precision == SE_F32_MIXED));
-    const DevTiles &P = *b->plan;
     const bool f32 = p->precision == SE_F32_MIXED;
+    se_batch::Exec *x = nullptr;
+    SE_TRY(batch_exec(b, f32, s, &x));
+    const DevTiles &P = *x->plan;
     if (!(f32 ? P.ok32 : P.ok64)) {
         set_error("se_subcycle_batched: plan does not fit this precision");
         return SE_ERR_ARG;
@@ -2256,8 +2288,8 @@ se_status se_subcycle_batched(se_batch *b, const se_params *p, se_state *st, con
         Lmax = std::max(Lmax, Lm[i]);
         order[i] = static_cast<int32_t>(i);
     }
-    std::sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
-        return Lm[x] != Lm[y] ? Lm[x] > Lm[y] : b->mtiles[x] > b->mtiles[y];
+    std::sort(order.begin(), order.end(), [&](int32_t i, int32_t j) {
+        return Lm[i] != Lm[j] ? Lm[i] > Lm[j] : x->mtiles[i] > x->mtiles[j];
     });
     std::vector<int64_t> load(Lmax, 0);
     std::vector<int32_t> off(n, 0);
@@ -2273,16 +2305,16 @@ se_status se_subcycle_batched(se_batch *b, const se_params *p, se_state *st, con
             }
         }
         off[i] = best;
-        for (int32_t c = best; c < best + Lm[i]; ++c) load[c] += b->mtiles[i];
+        for (int32_t c = best; c < best + Lm[i]; ++c) load[c] += x->mtiles[i];
     }
     for (size_t i = 0; i < n; ++i) {
         tab[i] = make_step(p, nsub[i], dt[i]);
-        tab[i].ntiles = b->mtiles[i];
+        tab[i].ntiles = x->mtiles[i];
         tab[i].vol_off = L.vol_off[i];
         tab[i].chunk0 = off[i];
     }
-    const bool same = b->table_host.size() == n &&
-                      std::memcmp(b->table_host.data(), tab.data(), n * sizeof(StepC)) == 0;
+    const bool same = x->table_host.size() == n &&
+                      std::memcmp(x->table_host.data(), tab.data(), n * sizeof(StepC)) == 0;
     if (!same) {
         // new configuration: upload constants and per-launch tile lists
         HIP_TRY(hipStreamSynchronize(s), "batched: sync before table update");
@@ -2291,14 +2323,14 @@ se_status se_subcycle_batched(se_batch *b, const se_params *p, se_state *st, con
         for (int32_t c = 0; c < Lmax; ++c) {
             for (size_t i = 0; i < n; ++i)
                 if (c >= off[i] && c < off[i] + Lm[i])
-                    for (int32_t t = 0; t < b->mtiles[i]; ++t) lists.push_back(b->mtile_first[i] + t);
+                    for (int32_t t = 0; t < x->mtiles[i]; ++t) lists.push_back(x->mtile_first[i] + t);
             loff.push_back(static_cast<int32_t>(lists.size()));
         }
-        SE_TRY(b->table.upload(tab.data(), n * sizeof(StepC)));
-        SE_TRY(b->lists.upload(lists.data(), std::max<size_t>(lists.size(), 1) * 4));
-        b->list_off = loff;
-        b->table_host = tab;
-        b->drop_graphs();
+        SE_TRY(x->table.upload(tab.data(), n * sizeof(StepC)));
+        SE_TRY(x->lists.upload(lists.data(), std::max<size_t>(lists.size(), 1) * 4));
+        x->list_off = loff;
+        x->table_host = tab;
+        x->drop_graphs();
     }
     // epilogue tables: volume rows per member, and the word ranges of the members
     // whose last chunk wrote the workspace buffers (an odd number of chunks)
@@ -2310,7 +2342,7 @@ se_status se_subcycle_batched(se_batch *b, const se_params *p, se_state *st, con
         VolMember vm{};
         vm.part_off = L.vol_off[i];
         vm.out_off = vrows;
-        vm.width = b->mtiles[i];
+        vm.width = x->mtiles[i];
         vm.row0 = vrows;
         vm.add = f32 ? p->eta_ref * b->atot[i] : 0.0;
         vt.push_back(vm);
@@ -2332,16 +2364,16 @@ se_status se_subcycle_batched(se_batch *b, const se_params *p, se_state *st, con
         return x.size() != y.size() ||
                (!x.empty() && std::memcmp(x.data(), y.data(), x.size() * sizeof(x[0])) != 0);
     };
-    if (differs(vt, b->voltab_host) || differs(ct, b->cpytab_host)) {
+    if (differs(vt, x->voltab_host) || differs(ct, x->cpytab_host)) {
         HIP_TRY(hipStreamSynchronize(s), "batched: sync before epilogue table update");
-        b->drop_graphs();
-        SE_TRY(b->voltab.upload(vt.data(), vt.size() * sizeof(VolMember)));
+        x->drop_graphs();
+        SE_TRY(x->voltab.upload(vt.data(), vt.size() * sizeof(VolMember)));
         if (ct.empty())
-            SE_TRY(b->cpytab.alloc(sizeof(CopyRange)));   // never read (no ranges)
+            SE_TRY(x->cpytab.alloc(sizeof(CopyRange)));   // never read (no ranges)
         else
-            SE_TRY(b->cpytab.upload(ct.data(), ct.size() * sizeof(CopyRange)));
-        b->voltab_host = vt;
-        b->cpytab_host = ct;
+            SE_TRY(x->cpytab.upload(ct.data(), ct.size() * sizeof(CopyRange)));
+        x->voltab_host = vt;
+        x->cpytab_host = ct;
     }
     char *w = static_cast<char *>(ws);
     TileArgs a{};
@@ -2357,7 +2389,7 @@ se_status se_subcycle_batched(se_batch *b, const se_params *p, se_state *st, con
     a.lgeo = f32 ? P.geo32.p : P.geo64.p;
     a.lae = f32 ? P.ae32.p : P.ae64.p;
     a.lv_av = f32 ? P.lav32.p : P.lav64.p;
-    a.mem = b->table.as<const StepC>();
+    a.mem = x->table.as<const StepC>();
     a.R = fo->R;
     a.f = fo->f;
     a.H0 = fo->H0;
@@ -2386,10 +2418,10 @@ se_status se_subcycle_batched(se_batch *b, const se_params *p, se_state *st, con
 
     auto enqueue = [&]() -> se_status {
         for (int32_t c = 0; c < Lmax; ++c) {
-            const int32_t cnt = b->list_off[c + 1] - b->list_off[c];
+            const int32_t cnt = x->list_off[c + 1] - x->list_off[c];
             if (cnt == 0) continue;
             a.chunk = c;
-            a.tile_list = b->lists.as<const int32_t>() + b->list_off[c];
+            a.tile_list = x->lists.as<const int32_t>() + x->list_off[c];
             a.ntiles = cnt;
             HIP_TRY(launch_tile(f32, 0, P.ept, P.block, a, cnt, lds, s), "batched launch");
         }
@@ -2397,11 +2429,11 @@ se_status se_subcycle_batched(se_batch *b, const se_params *p, se_state *st, con
                                    static_cast<uint32_t *>(st->eta),
                                    reinterpret_cast<const uint32_t *>(w + L.U_alt),
                                    static_cast<uint32_t *>(st->U),
-                                   b->cpytab.as<const CopyRange>(),
-                                   static_cast<int32_t>(b->cpytab_host.size()), cwords, s),
+                                   x->cpytab.as<const CopyRange>(),
+                                   static_cast<int32_t>(x->cpytab_host.size()), cwords, s),
                 "batched copy of final states");
         if (st->volume)
-            HIP_TRY(launch_vol_reduce_batch(a.vol_part, b->voltab.as<const VolMember>(),
+            HIP_TRY(launch_vol_reduce_batch(a.vol_part, x->voltab.as<const VolMember>(),
                                             static_cast<int32_t>(n), vrows, st->volume, s),
                     "batched volume");
         return SE_OK;
@@ -2415,7 +2447,7 @@ se_status se_subcycle_batched(se_batch *b, const se_params *p, se_state *st, con
         reinterpret_cast<uint64_t>(fo->H0), reinterpret_cast<uint64_t>(fo->W),
         reinterpret_cast<uint64_t>(ws), reinterpret_cast<uint64_t>(s),
         static_cast<uint64_t>(p->precision), static_cast<uint64_t>(p->flags)};
-    for (auto &gr : b->graphs) {
+    for (auto &gr : x->graphs) {
         if (gr.key == key) {
             HIP_TRY(hipGraphLaunch(gr.x, s), "batched graph launch");
             return SE_OK;
@@ -2434,7 +2466,7 @@ se_status se_subcycle_batched(se_batch *b, const se_params *p, se_state *st, con
     if (ee != hipSuccess) return hip_fail(ee, "end capture");
     gr.g = g;
     HIP_TRY(hipGraphInstantiate(&gr.x, g, nullptr, nullptr, 0), "graph instantiate");
-    b->graphs.push_back(gr);
+    x->graphs.push_back(gr);
     HIP_TRY(hipGraphLaunch(gr.x, s), "batched graph launch");
     return SE_OK;
 }
@@ -2451,7 +2483,14 @@ se_status se_batch_set_plan_impl(se_batch *b, int32_t tile, int32_t k_fused, int
         return SE_OK;
     }
     DeviceGuard dg(b->device);
-    return batch_install_plan(b, tile, k_fused, block);
+    std::unique_ptr<DevTiles> p;
+    SE_TRY(make_plan(batch_members(b), b->voff, b->eoff, tile, k_fused, block, p));
+    const std::shared_ptr<DevTiles> sp = std::move(p);
+    for (se_batch::Exec &x : b->exec) batch_use_plan(b, x, sp);
+    b->plan_T = tile;
+    b->plan_K = k_fused;
+    b->plan_block = block;
+    return SE_OK;
 }
 
 se_status se_batch_get_plan_impl(const se_batch *b, int32_t *tile, int32_t *k_fused,

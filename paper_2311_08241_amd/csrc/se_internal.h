@@ -111,6 +111,9 @@ se_status build_tiles(const std::vector<const HostMesh *> &members,
 struct DevBuf {
     void *p = nullptr;
     size_t n = 0;
+    DevBuf() = default;
+    DevBuf(const DevBuf &) = delete;
+    DevBuf &operator=(const DevBuf &) = delete;
     ~DevBuf();
     se_status alloc(size_t bytes);
     se_status upload(const void *src, size_t bytes);
@@ -148,6 +151,13 @@ struct DevTiles {
     DevBuf vnb, vgeo64, vgeo32;
 };
 
+// Tile tables of the trim/z* consumer (TrimTiles); no tiles: the mesh has a row beyond the
+// capacity.
+struct DevTrimTiles {
+    DevBuf hdr, lv, le, rloc;
+    int32_t ntiles = 0;
+};
+
 // Mesh geometry and connectivity on the device (global numbering).
 struct DevMesh {
     int64_t nv = 0, ne = 0;
@@ -159,11 +169,10 @@ struct DevMesh {
     // edge (l, l/d) [ne][3][2] in FP64 and FP32
     DevBuf vnb, vgeo64, vgeo32;
     // trim/z* consumer, built on first use: sub-cell flux vectors [ne][3][2] FP64; the
-    // tile tables (TrimTiles) for the triangle capacity tt_cap_e (0: not built, -1: the
-    // mesh has a row beyond it) and local vertex capacity tt_cap_v
+    // tile tables of each capacity that some layer count has asked for (kept, so that
+    // calls of different layer counts do not build each other's anew)
     DevBuf slotS;
-    DevBuf tt_hdr, tt_lv, tt_le, tt_rloc;
-    int32_t tt_cap_e = 0, tt_cap_v = 0, tt_ntiles = 0;
+    std::map<int32_t, std::unique_ptr<DevTrimTiles>> trim_tiles;   // by triangles per tile
 };
 
 // The forward subcycle on the tile kernel (se_subcycle); may_alloc false: fail instead

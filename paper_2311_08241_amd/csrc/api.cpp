@@ -1417,17 +1417,17 @@ se_status se_subcycle_plain(se_mesh *m, const se_params *p, se_state *st, const 
     return SE_OK;
 }
 
-// Tile tables of the trim for cap_e local triangles and cap_v local vertices per tile, built
-// at the first call that asks for them.
-static se_status ensure_trim_tiles(se_mesh *m, int cap_e, int cap_v, const DevTrimTiles **out) {
-    const auto it = m->d.trim_tiles.find(cap_e);
+// Tile tables of the trim for cap local triangles and vertices per tile, built at the first
+// call that asks for them.
+static se_status ensure_trim_tiles(se_mesh *m, int cap, const DevTrimTiles **out) {
+    const auto it = m->d.trim_tiles.find(cap);
     if (it != m->d.trim_tiles.end()) {
         *out = it->second.get();
         return SE_OK;
     }
     TrimTiles tt;
     auto d = std::make_unique<DevTrimTiles>();
-    if (build_trim_tiles(m->h, cap_e, kTrimTileOwn, cap_v, tt)) {
+    if (build_trim_tiles(m->h, cap, kTrimTileOwn, cap, tt)) {
         SE_TRY(d->hdr.upload(tt.hdr.data(), tt.hdr.size() * 4));
         SE_TRY(d->lv.upload(tt.lv.data(), tt.lv.size() * 4));
         SE_TRY(d->le.upload(tt.le.data(), tt.le.size() * 4));
@@ -1435,7 +1435,7 @@ static se_status ensure_trim_tiles(se_mesh *m, int cap_e, int cap_v, const DevTr
         d->ntiles = tt.ntiles;
     }
     *out = d.get();
-    m->d.trim_tiles[cap_e] = std::move(d);
+    m->d.trim_tiles[cap] = std::move(d);
     return SE_OK;
 }
 
@@ -1485,16 +1485,22 @@ se_status se_trim_zstar(se_mesh *m, int32_t K, const double *H0, const double *e
     }
     // the tile form (one launch), unless U is Ustar itself (a tile would overwrite
     // transports that a later tile still reads) or one vertex's row exceeds a tile
-    const int cap_e = trim_tile_cap_e(K), cap_v = trim_tile_cap_v(K);
     const DevTrimTiles *T = nullptr;
-    if (U != Ustar) SE_TRY(ensure_trim_tiles(m, cap_e, cap_v, &T));
+    int cap = trim_tile_cap_e(K);
+    if (U != Ustar) {
+        SE_TRY(ensure_trim_tiles(m, cap, &T));
+        if (T->ntiles == 0 && trim_tile_cap_wide(K) > 0) {
+            cap = trim_tile_cap_wide(K);
+            SE_TRY(ensure_trim_tiles(m, cap, &T));
+        }
+    }
     if (T && T->ntiles > 0) {
         a.tt_hdr = T->hdr.as<const int32_t>();
         a.tt_lv = T->lv.as<const int32_t>();
         a.tt_le = T->le.as<const int2>();
         a.tt_rloc = T->rloc.as<const uint16_t>();
         a.tt_ntiles = T->ntiles;
-        a.tt_cap_v = cap_v;
+        a.tt_cap_v = cap;
         HIP_TRY(launch_trim_tile(a, m->d.slotS.as<const double>(), s), "se_trim_zstar launch");
         return SE_OK;
     }

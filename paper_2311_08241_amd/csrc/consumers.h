@@ -28,9 +28,10 @@ struct TrimArgs {
 };
 // S: per-triangle sub-cell flux vectors [ne][3][2], S_k = -A_e grad N_k
 hipError_t launch_trim(const TrimArgs &a, const double *S, hipStream_t s);
-// Tile form: triangles (local ones) per tile and local vertices per tile for K layers
+// Tile form: local triangles (and local vertices) per tile for K layers, and of the larger
+// tiles for meshes with a row beyond those (0: none)
 int trim_tile_cap_e(int K);
-int trim_tile_cap_v(int K);
+int trim_tile_cap_wide(int K);
 constexpr int kTrimTileOwn = 64;   // own vertices per tile
 hipError_t launch_trim_tile(const TrimArgs &a, const double *S, hipStream_t s);
 

@@ -301,6 +301,11 @@ constexpr int TT_VPG = kTrimTileOwn / 32;   // own vertices per group
 // 96-triangle ones at K = 40 despite their larger halo; with one triangle per group more at
 // L = 3 and 4 the rounds spill (550k vertices: K = 24 347 us, 311 now; K = 32 442, 388).
 template <int L> constexpr int trim_tpg() { return L <= 1 ? 8 : L <= 2 ? 4 : L <= 3 ? 3 : 2; }
+// One triangle per group more at L = 3 and 4, three workgroups per CU, for a mesh with a row
+// that exceeds the tiles above (97 to 128 and 65 to 96 triangles); 0: none.  224,001 vertices
+// with a row of 120 triangles, K = 20 142 us (three launches 223), K = 24 148 (236); with a
+// row of 80, K = 28 189 (275), K = 32 185 (279).
+template <int L> constexpr int trim_wide() { return L == 3 || L == 4 ? trim_tpg<L>() + 1 : 0; }
 
 // Layer blocks per round of step 3 and the doubles of the vertex columns or a round's
 // transports, whichever are more (the transports lie over the columns, which step 2 has
@@ -309,19 +314,19 @@ template <int L> constexpr int trim_tpg() { return L <= 1 ? 8 : L <= 2 ? 4 : L <
 // every row entry instead of 10 and 5, in less LDS (550k vertices: 557 -> 537 us).  Three
 // blocks of 128-triangle tiles would leave two workgroups per CU (K = 24, 550k vertices,
 // before the loads were batched: 336 us; 465 with three, 390 with one block per round).
-template <int L> constexpr int trim_nb() {
-    constexpr int CE = 32 * trim_tpg<L>();
+template <int L, int TPG> constexpr int trim_nb() {
+    constexpr int CE = 32 * TPG;
     constexpr int fit = (40 * 1024 - CE * 54) / (CE * 128), most = fit < 1 ? 1 : fit < L ? fit : L;
     constexpr int rounds = (L + most - 1) / most;
     return (L + rounds - 1) / rounds;
 }
 template <int L, int TPG> __host__ __device__ constexpr size_t trim_cols(int cap_v, int K) {
-    const size_t cols = static_cast<size_t>(cap_v) * K, rnd = trim_nb<L>() * 32 * TPG * 16;
+    const size_t cols = static_cast<size_t>(cap_v) * K, rnd = trim_nb<L, TPG>() * 32 * TPG * 16;
     return ((cols > rnd ? cols : rnd) + 1) & ~static_cast<size_t>(1);
 }
 
 template <int L, int TPG>
-__global__ void __launch_bounds__(256, L >= 2 && L <= 5 ? 4 : 3)
+__global__ void __launch_bounds__(256, L >= 2 && L <= 5 && TPG == trim_tpg<L>() ? 4 : 3)
     k_trim_tile(TrimArgs a, const double *S) {
     extern __shared__ __align__(16) double tsm[];
     const int tid = threadIdx.x, g = tid & 7, grp = tid >> 3;
@@ -331,7 +336,7 @@ __global__ void __launch_bounds__(256, L >= 2 && L <= 5 ? 4 : 3)
     const int32_t nel = hd[2] & 0xffff, neo = hd[2] >> 16;
     const int32_t lv_off = hd[3], le_off = hd[4], nent = hd[5], jb = hd[6];
     constexpr int CE = 32 * TPG;
-    constexpr int NB = trim_nb<L>();
+    constexpr int NB = trim_nb<L, TPG>();
     double *sP = tsm;                             // [cap_v][K], then, over it,
     d2v *sU = reinterpret_cast<d2v *>(tsm);       // [NB][CE][8]
     d2v *sS = reinterpret_cast<d2v *>(tsm + trim_cols<L, TPG>(a.tt_cap_v, K));   // [3 CE]
@@ -772,10 +777,16 @@ int trim_tile_cap_e(int K) {
         default: return 32 * trim_tpg<8>();
     }
 }
-int trim_tile_cap_v(int K) { return trim_tile_cap_e(K); }
+int trim_tile_cap_wide(int K) {
+    switch ((K + 7) / 8) {
+        case 3: return 32 * trim_wide<3>();
+        case 4: return 32 * trim_wide<4>();
+        default: return 0;
+    }
+}
 
-template <int L> hipError_t launch_trim_tile_l(const TrimArgs &a, const double *S, hipStream_t s) {
-    constexpr int TPG = trim_tpg<L>();
+template <int L, int TPG>
+hipError_t launch_trim_tile_t(const TrimArgs &a, const double *S, hipStream_t s) {
     constexpr int CE = 32 * TPG;
     const size_t lds = trim_cols<L, TPG>(a.tt_cap_v, a.K) * 8 + CE * (3 * 16 + 3 * 2);
     hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(k_trim_tile<L, TPG>),
@@ -786,8 +797,16 @@ template <int L> hipError_t launch_trim_tile_l(const TrimArgs &a, const double *
     return hipGetLastError();
 }
 
+template <int L> hipError_t launch_trim_tile_l(const TrimArgs &a, const double *S, hipStream_t s) {
+    if constexpr (trim_wide<L>() > 0)
+        if (a.tt_cap_v == 32 * trim_wide<L>()) return launch_trim_tile_t<L, trim_wide<L>()>(a, S, s);
+    return launch_trim_tile_t<L, trim_tpg<L>()>(a, S, s);
+}
+
 hipError_t launch_trim_tile(const TrimArgs &a, const double *S, hipStream_t s) {
-    if (a.K < 1 || a.K > 64 || a.tt_cap_v != trim_tile_cap_v(a.K)) return hipErrorInvalidValue;
+    if (a.K < 1 || a.K > 64 || a.tt_cap_v <= 0 ||
+        (a.tt_cap_v != trim_tile_cap_e(a.K) && a.tt_cap_v != trim_tile_cap_wide(a.K)))
+        return hipErrorInvalidValue;
     if (a.tt_ntiles <= 0) return hipSuccess;
     switch ((a.K + 7) / 8) {
         case 1: return launch_trim_tile_l<1>(a, S, s);

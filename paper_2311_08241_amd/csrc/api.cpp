@@ -210,10 +210,13 @@ bool adj_fits(bool f32, int32_t max_nv, int32_t max_nvu, int32_t max_cs, int32_t
            adj_tile_lds_bytes(f32, block, K, max_nv, max_nvu, max_cs) <= 160 * 1024;
 }
 
-// Upload a tile plan built by plan_host (ht is used up).
+// Upload a tile plan built by plan_host (ht is used up).  Values go up for the precisions in
+// precs alone (bit 0: FP64, bit 1: FP32); the plan does not run in the other.
 se_status upload_plan(const std::vector<const HostMesh *> &members, const std::vector<int64_t> &voff,
                       const std::vector<int64_t> &eoff, int32_t T, int32_t K, int32_t block,
-                      HostTiles &ht, const se_plan_stats_t &st, std::unique_ptr<DevTiles> &out) {
+                      HostTiles &ht, const se_plan_stats_t &st, int precs,
+                      std::unique_ptr<DevTiles> &out) {
+    const bool with64 = precs & 1, with32 = precs & 2;
     const int ept = st.tri_per_thread;
     if (!st.ok_f32 && !st.ok_f64) {
         set_error("se_set_plan: tile too large for the register or LDS budget (reduce tile or "
@@ -260,12 +263,12 @@ se_status upload_plan(const std::vector<const HostMesh *> &members, const std::v
     p->ell = ht.ell;
     p->lds_bytes64 = st.lds_f64;
     p->lds_bytes32 = st.lds_f32;
-    p->ok32 = st.ok_f32;
-    p->ok64 = st.ok_f64;
+    p->ok32 = st.ok_f32 && with32;
+    p->ok64 = st.ok_f64 && with64;
     p->lds_sm32 = st.lds_sesm_f32;
     p->lds_sm64 = st.lds_sesm_f64;
-    p->ok_sm32 = st.ok_sesm_f32;
-    p->ok_sm64 = st.ok_sesm_f64;
+    p->ok_sm32 = st.ok_sesm_f32 && with32;
+    p->ok_sm64 = st.ok_sesm_f64 && with64;
     p->hdr_host = ht.hdr;
     p->le_gid_host = ht.le_gid;
     p->nE_host = ht.nE;
@@ -287,20 +290,22 @@ se_status upload_plan(const std::vector<const HostMesh *> &members, const std::v
     }
     SE_TRY(p->cs_row.upload(ht.cs_row.data(), ht.cs_row.size() * 2));
     // local geometry per tile, gathered member by member
-    std::vector<double> g64(4 * nle), a64e(nle);
-    std::vector<float> g32(4 * nle), a32e(nle);
+    std::vector<double> g64(with64 ? 4 * nle : 0), a64e(with64 ? nle : 0);
+    std::vector<float> g32(with32 ? 4 * nle : 0), a32e(with32 ? nle : 0);
     for (int64_t i = 0; i < nle; ++i) {
         const int64_t ge = ht.le_gid[i];
         size_t mi = std::upper_bound(eoff.begin(), eoff.end(), ge) - eoff.begin() - 1;
         const HostMesh &m = *members[mi];
         const int64_t e = ge - eoff[mi];
         const double *gn = &m.gN[6 * e];
-        for (int q = 0; q < 4; ++q) {
-            g64[4 * i + q] = gn[2 + q];
-            g32[4 * i + q] = static_cast<float>(gn[2 + q]);
+        if (with64) {
+            for (int q = 0; q < 4; ++q) g64[4 * i + q] = gn[2 + q];
+            a64e[i] = m.Ae[e];
         }
-        a64e[i] = m.Ae[e];
-        a32e[i] = static_cast<float>(m.Ae[e]);
+        if (with32) {
+            for (int q = 0; q < 4; ++q) g32[4 * i + q] = static_cast<float>(gn[2 + q]);
+            a32e[i] = static_cast<float>(m.Ae[e]);
+        }
     }
     SE_TRY(p->geo64.upload(g64.data(), g64.size() * 8));
     SE_TRY(p->geo32.upload(g32.data(), g32.size() * 4));
@@ -309,17 +314,17 @@ se_status upload_plan(const std::vector<const HostMesh *> &members, const std::v
     // reciprocal dual-cell areas per local vertex (contiguous per tile: no index round
     // trip); FP32: of the FP32-rounded area, rounded once
     const int64_t nlv = static_cast<int64_t>(ht.lv_gid.size());
-    std::vector<double> a64(nlv);
-    std::vector<float> a32(nlv);
+    std::vector<double> a64(with64 ? nlv : 0);
+    std::vector<float> a32(with32 ? nlv : 0);
     for (int64_t i = 0; i < nlv; ++i) {
         const int64_t gv = ht.lv_gid[i];
         size_t mi = std::upper_bound(voff.begin(), voff.end(), gv) - voff.begin() - 1;
         const double av = members[mi]->Av[gv - voff[mi]];
-        a64[i] = 1.0 / av;
-        a32[i] = 1.0f / static_cast<float>(av);
+        if (with64) a64[i] = 1.0 / av;
+        if (with32) a32[i] = 1.0f / static_cast<float>(av);
     }
-    SE_TRY(p->lav64.upload(a64.data(), nlv * 8));
-    SE_TRY(p->lav32.upload(a32.data(), nlv * 4));
+    SE_TRY(p->lav64.upload(a64.data(), a64.size() * 8));
+    SE_TRY(p->lav32.upload(a32.data(), a32.size() * 4));
     // raise the LDS limit of the forward-backward tile kernels this plan runs now, so
     // that a later launch needs no attribute call (the adjoint may be graph-captured)
     for (int f = 0; f < 2; ++f)
@@ -346,7 +351,7 @@ se_status make_plan(const std::vector<const HostMesh *> &members, const std::vec
     HostTiles ht;
     se_plan_stats_t st;
     SE_TRY(plan_host(members, voff, eoff, T, K, block, ht, st));
-    return upload_plan(members, voff, eoff, T, K, block, ht, st, out);
+    return upload_plan(members, voff, eoff, T, K, block, ht, st, 3, out);
 }
 
 // LDS of the viscous form of a plan whose forward-backward form takes lds bytes: the
@@ -753,7 +758,9 @@ const std::vector<PlanCand> kAnyPlans = {
     {1024, 4, 512, 8, 0}, {512, 4, 512, 8, 0}, {512, 4, 256, 8, 0}, {512, 2, 256, 8, 0},
     {256, 4, 256, 8, 0},  {256, 2, 256, 8, 0}, {128, 2, 256, 8, 0}, {64, 1, 256, 8, 0}};
 
-// Build the first candidate that fits the form on this mesh.
+// Build the first candidate that fits the form on this mesh, with the tables of the form's own
+// precision (half of the memory and of the upload of both); of both where the plan is one for
+// every form, or runs every form and any_ok is asked for.
 se_status make_default(se_mesh *m, int cl, const std::vector<PlanCand> &cand,
                        std::unique_ptr<DevTiles> &out, bool *any_ok) {
     const std::vector<const HostMesh *> mem{&m->h};
@@ -770,7 +777,8 @@ se_status make_default(se_mesh *m, int cl, const std::vector<PlanCand> &cand,
             !plan_fits(cl, ht, st, c.K, c.block))
             continue;
         if (any_ok) *any_ok = plan_fits(CL_ANY, ht, st, c.K, c.block);
-        return upload_plan(mem, vo, eo, c.T, c.K, c.block, ht, st, out);
+        const int precs = cl >= CL_ANY || (any_ok && *any_ok) ? 3 : 1 << (cl & 1);
+        return upload_plan(mem, vo, eo, c.T, c.K, c.block, ht, st, precs, out);
     }
     set_error("no default plan fits this mesh");
     return SE_ERR_ARG;
@@ -819,7 +827,7 @@ se_status mesh_plan(se_mesh *m, int cl, bool may_alloc, hipStream_t s, DevTiles 
         return SE_OK;
     }
     cand.insert(cand.end(), kAnyPlans.begin(), kAnyPlans.end());
-    const se_status own = make_default(m, cl, cand, p, &any_ok);
+    const se_status own = make_default(m, cl, cand, p, any ? nullptr : &any_ok);
     if (!any && (own != SE_OK || !any_ok)) {
         // (a form whose own plan runs every form needs no second one)
         std::unique_ptr<DevTiles> a;
@@ -1532,8 +1540,8 @@ static se_status ensure_tile_visc(const se_mesh *m, DevTiles &P) {
     SE_TRY(build_visc_tables(m->h, nb4, vg));
     const int64_t nle = static_cast<int64_t>(P.le_gid_host.size());
     std::vector<uint32_t> tnb(2 * nle);
-    std::vector<double> tg64(6 * nle);
-    std::vector<float> tg32(6 * nle);
+    std::vector<double> tg64(P.ok64 ? 6 * nle : 0);   // of the precisions the plan runs in
+    std::vector<float> tg32(P.ok32 ? 6 * nle : 0);
     std::vector<int32_t> eloc(m->h.ne, -1);
     for (int32_t t = 0; t < P.ntiles; ++t) {
         const int64_t off = static_cast<int64_t>(t) * P.se;
@@ -1546,8 +1554,8 @@ static se_status ensure_tile_visc(const se_mesh *m, DevTiles &P) {
                 const int32_t g = nb4[4 * e + j];
                 l3[j] = (g >= 0 && eloc[g] >= 0) ? static_cast<uint32_t>(eloc[g]) : 0xffffu;
                 for (int k = 0; k < 2; ++k) {
-                    tg64[6 * (off + q) + 2 * j + k] = vg[6 * e + 2 * j + k];
-                    tg32[6 * (off + q) + 2 * j + k] = static_cast<float>(vg[6 * e + 2 * j + k]);
+                    if (P.ok64) tg64[6 * (off + q) + 2 * j + k] = vg[6 * e + 2 * j + k];
+                    if (P.ok32) tg32[6 * (off + q) + 2 * j + k] = static_cast<float>(vg[6 * e + 2 * j + k]);
                 }
             }
             tnb[2 * (off + q)] = l3[0] | (l3[1] << 16);
@@ -2116,7 +2124,7 @@ se_status batch_exec(se_batch *b, bool f32, hipStream_t s, se_batch::Exec **out)
             return SE_OK;
         }
         std::unique_ptr<DevTiles> p;
-        const se_status rc = upload_plan(batch_members(b), b->voff, b->eoff, c.T, c.K, c.block, ht, st, p);
+        const se_status rc = upload_plan(batch_members(b), b->voff, b->eoff, c.T, c.K, c.block, ht, st, 3, p);
         if (rc == SE_OK) {
             batch_use_plan(b, x, std::move(p));
             if (!other.plan) {

@@ -58,28 +58,22 @@ def _tier_ok(precision: str, ept: int, block: int) -> bool:
     return ept <= ((3 if sm else 4) if prec == "f32" else (1 if sm else 3))
 
 
-# VGPRs of the FP64 tile kernel per register tier, from the compiler's resource report
-# (the per-triangle indices and geometry are re-materialised every substep)
-_F64_VGPRS = {1: 82, 2: 101, 3: 127, 4: 157, 6: 215, 8: 256}
-# the same for the viscous form (FP32 up to three slots: the edge geometry held in
-# registers; the tiers the library refuses are never timed)
-_VISC_VGPRS = {"f32": {1: 72, 2: 102, 3: 127, 4: 141, 6: 189, 8: 239},
-               "f64": {1: 109, 2: 141, 3: 165, 4: 197, 6: 256, 8: 256}}
-# FP32 AB3-AM4 (four slots re-materialise their packed indices)
-_SESM32_VGPRS = {1: 65, 2: 89, 3: 111, 4: 124, 6: 188, 8: 240}
+# VGPRs of the tile kernel per form and register tier, from the compiler's resource report (the
+# tiers the library refuses are never timed)
+_VGPRS = {
+    "f32": {1: 63, 2: 83, 3: 102, 4: 126, 6: 177, 8: 231},
+    "f64": {1: 72, 2: 102, 3: 126, 4: 158, 6: 222, 8: 256},
+    "f32-sesm": {1: 65, 2: 90, 3: 111, 4: 124, 6: 188, 8: 240},
+    "f64-sesm": {1: 93, 2: 144, 3: 188, 4: 239, 6: 256, 8: 256},
+    "f32-visc": {1: 68, 2: 97, 3: 123, 4: 143, 6: 197, 8: 251},
+    "f64-visc": {1: 99, 2: 135, 3: 167, 4: 203, 6: 256, 8: 256},
+}
 
 
 def _vgprs(precision: str, ept: int) -> int:
-    """Approximate VGPRs of the tile kernel per register tier (measured from the
-    compiler's resource report: about 24 per triangle slot in FP32, 51 in FP64 AB3-AM4;
-    FP64 forward-backward, FP32 AB3-AM4 and viscous tiers tabulated)."""
+    """VGPRs of the tile kernel per register tier, as allocated (units of 8)."""
     prec, sm = _split(precision)
-    if _visc(precision):
-        v = _VISC_VGPRS[prec][ept]
-    elif prec == "f32":
-        v = _SESM32_VGPRS[ept] if sm else 32 + 24 * ept
-    else:
-        v = 52 + 51 * ept if sm else _F64_VGPRS[ept]
+    v = _VGPRS[prec + ("-sesm" if sm else "-visc" if _visc(precision) else "")][ept]
     return -(-v // 8) * 8
 
 

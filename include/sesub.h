@@ -209,7 +209,10 @@ se_status se_subcycle(se_mesh *mesh, const se_params *params, se_state *state,
  * array on every device it runs on, until the process ends.  Nothing is allocated:
  * the mesh must already have a tile plan (se_set_plan, or an earlier se_subcycle
  * call), and with the viscous term its tables must already exist (an earlier
- * se_subcycle call with the term builds them).  All calls on one device share that
+ * se_subcycle call with the term, in either precision, builds them).  A form (scheme,
+ * precision, viscous term) that has not yet run by se_subcycle on the mesh uses the default
+ * plan that runs every form, slower than its own (small meshes: up to twice the time); so
+ * does a first se_subcycle call under stream capture.  All calls on one device share that
  * device's array and find the last call's contents in it (the subcycle writes every
  * part of its workspace before reading it, so nothing needs clearing); calls that
  * overlap on one device (several streams or host threads) race and must be
@@ -234,8 +237,10 @@ se_status se_subcycle_plain(se_mesh *mesh, const se_params *params, se_state *st
  * Seeds may be NULL (zero); outputs may be NULL (not computed).  ckpt_every
  * (1 <= ckpt_every <= nsub) sets the workspace: a checkpoint every ckpt_every substeps
  * and two segments of states.  On a tile plan the forward elevations of all substeps are
- * kept instead where they fit that workspace (up to about 180 substeps for any
- * ckpt_every); else the trajectory is recomputed from the checkpoints, each segment in the
+ * kept instead where they fit that workspace,
+ *   nsub nv <= (ceil(nsub / ckpt_every) + 2 ckpt_every - 2) (nv + 2 ne),
+ * which holds for any ckpt_every up to about 180 substeps on a mesh of two triangles per
+ * vertex; else the trajectory is recomputed from the checkpoints, each segment in the
  * same launches as the reverse substeps of the segment after it.  Gradients do not depend
  * on it.  eta0/U0 are the forward inputs and are not
  * modified.  Element types follow params.precision; lam_Uavg is double. */
@@ -268,10 +273,12 @@ se_status se_subcycle_batched(se_batch *batch, const se_params *params, se_state
 /* Execution plan of the temporally blocked kernel: tile = vertices per
  * tile (64..8192), k_fused = substeps per launch (1..8), block = threads per
  * workgroup (256, 512 or 1024).  Applies to a mesh (kind 0) or a batch (kind 1).
- * Without one, each form of the subcycle makes a default plan from the number of vertices
- * at its first call (the adjoint once a forward call has made one; per-substep kernels
- * before); se_set_plan replaces them all.  The fields do not depend on the plan, the
- * volume to rounding.
+ * Without one, each form of the subcycle (forward-backward, AB3-AM4, viscous; FP64, FP32)
+ * makes a default plan from the number of vertices at its first call, which takes some tenths
+ * of a second on millions of vertices, and the first of a mesh one that runs every form
+ * besides; the adjoint does once a forward call has (per-substep kernels before), a batch per
+ * precision.  se_set_plan replaces them all; se_get_plan reports the caller's plan, else the
+ * default made first.  The fields do not depend on the plan, the volume to rounding.
  * Returns SE_ERR_ARG if the plan does not fit the kernel's register or LDS
  * budget for this mesh. */
 se_status se_set_plan(void *mesh_or_batch, int32_t kind, int32_t tile, int32_t k_fused,

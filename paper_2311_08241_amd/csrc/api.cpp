@@ -1138,7 +1138,6 @@ static TileArgs tile_args(const se_mesh *m, const DevTiles &P, bool f32, const s
     a.f = fo->f;
     a.H0 = fo->H0;
     a.W = fo->W;
-    a.Av = f32 ? m->d.Av32.p : m->d.Av64.p;
     a.Av64 = m->d.Av64.as<const double>();
     a.sum = w + L.sum;
     a.U0c = w + L.U0c;
@@ -1149,11 +1148,14 @@ static TileArgs tile_args(const se_mesh *m, const DevTiles &P, bool f32, const s
     a.ksub = P.K;
     a.ntiles = P.ntiles;
     a.xcd = 1;
-    // tables loaded ahead of the header when the tiles leave half of the CUs idle: the launch
-    // then lasts as long as one tile's chain of round trips (2,048 vertices 90.5 -> 88.4 us
-    // per call, 11,397 106.9 -> 104.1).  More tiles load against each other and lose by
-    // reading the padding and owned ids (242 tiles FP64 143.2 -> 143.5 at 5 rings, 139.2 ->
-    // 146.7 at 6; 1,039 tiles FP32 578 -> 585; an uneven ensemble 610 -> 648).
+    // tables loaded ahead of the header on launches of few tiles, which last as long as one
+    // tile's chain of round trips: 60 substeps, us, after the header / ahead of it, 32 tiles
+    // (2,048 vertices) FP32 92.5 / 90.5, FP64 96.7 / 92.1, viscous FP32 203 / 197, 113 tiles
+    // (7,200) 94.3 / 92.4, 99.7 / 94.5, 207 / 202.  The price is the padding and the owned ids
+    // that are read besides: tiles of 64 to 112 vertices gain up to 250 of them (16,000 vertices
+    // FP64 100.2 / 94.7, 27,000 110.9 / 107.8), 250 tiles of 200 vertices lose (50,000 FP64
+    // 130.4 / 136.1) and so do launches of more tiles than CUs (1,039 tiles FP32 578 / 585).
+    // Up to 128 no mesh loses.
     a.early = P.ntiles <= 128 ? 1 : 0;
     a.cap_nv = P.max_nv;
     a.cap_ne = P.max_ne;
@@ -1738,8 +1740,9 @@ se_status se_subcycle_adjoint(se_mesh *m, const se_params *p, const void *eta0, 
     // less.  Where those of all substeps and two states for the forward launches to
     // alternate between fit the bytes that the checkpoints and segment buffers of this
     // ckpt_every take, the step is one segment: no substep runs forward twice and the
-    // reverse launches are not cut at checkpoints (always so up to about 180 substeps;
-    // 65,536 vertices FP64, M = 30, ckpt_every 5, one gradient: 220 -> 154 us).
+    // reverse launches are not cut at checkpoints (with two triangles per vertex so at any
+    // ckpt_every up to about 180 substeps, on a strip of one triangle per vertex up to about
+    // 60; 65,536 vertices FP64, M = 30, ckpt_every 5, one gradient: 220 -> 154 us).
     const size_t whole = al(static_cast<size_t>(nsub) * nv * es) + 2 * st_bytes;
     if (rev_tiles && A.nseg > 1 && A.ckpt + whole <= A.lam_eta) {
         A.k = nsub;
@@ -2417,7 +2420,6 @@ se_status se_subcycle_batched(se_batch *b, const se_params *p, se_state *st, con
     a.f = fo->f;
     a.H0 = fo->H0;
     a.W = fo->W;
-    a.Av = f32 ? b->Av32.p : b->Av64.p;
     a.Av64 = b->Av64.as<const double>();
     a.sum = w + L.sum;
     a.U0c = w + L.U0c;

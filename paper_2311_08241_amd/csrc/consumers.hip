@@ -296,10 +296,13 @@ __global__ void __launch_bounds__(256) k_zstar_w(TrimArgs a, const double *S) {
 constexpr int TT_VPG = kTrimTileOwn / 32;   // own vertices per group
 
 // triangles per group: the trimmed transports of a group's triangles sit in registers
-// (4 TPG L VGPRs), beside a round's loads; within 128 VGPRs up to L = 5, so that four
-// workgroups share a CU, within 168 beyond (three).  64-triangle tiles ran 8% faster than
-// 96-triangle ones at K = 40 despite their larger halo; with one triangle per group more at
-// L = 3 and 4 the rounds spill (550k vertices: K = 24 347 us, 311 now; K = 32 442, 388).
+// (4 TPG L VGPRs), beside a round's loads; within 128 VGPRs for L = 2 to 5, so that four
+// workgroups share a CU, within 168 for the others (three; at L = 1 46 KB of LDS say so too).
+// 64-triangle tiles ran 8% faster than 96-triangle ones at K = 40 despite their larger halo;
+// with one triangle per group more at L = 3 and 4 the rounds spill at four workgroups (550k
+// vertices: K = 24 347 us, 311 now; K = 32 442, 388).  L = 8 keeps 20 bytes per lane in
+// scratch: loading <<U>> or the row entries after the columns avoids that and is slower
+// (224,001 vertices, K = 64: 334 us, 338 and 340 without).
 template <int L> constexpr int trim_tpg() { return L <= 1 ? 8 : L <= 2 ? 4 : L <= 3 ? 3 : 2; }
 // One triangle per group more at L = 3 and 4, three workgroups per CU, for a mesh with a row
 // that exceeds the tiles above (97 to 128 and 65 to 96 triangles); 0: none.  224,001 vertices
@@ -647,6 +650,13 @@ __global__ void __launch_bounds__(256) k_visc(ViscArgs a) {
 // that layer again and adds nothing): one memory round trip for a column of up to 40
 // layers, where a loop of four layers and a remainder, with a branch per array, made up to
 // six (550k vertices, K = 40, three arrays: 316 -> 282 us, 5.6 TB/s; K = 7, 300k: 40 -> 29).
+// The loads are non-temporal whatever the size.  Three arrays of K = 40 in all, us, the loop /
+// ordinary loads in one round / non-temporal ones, for columns that were read before, were
+// just written, and with 512 MiB written since:
+//   224 MiB   37.8 / 38.1 / 37.8   39.9 / 38.7 / 41.2   98.7 / 95.4 / 53.5
+//   449 MiB   89.1 / 86.9 / 75.4    123 /  120 / 81.4    149 /  143 /  103
+//   1953 MiB   372 /  368 /  320    431 /  426 /  425    432 /  425 /  446
+// (112 MiB, K = 20: 27.7 / 21.3 / 23.7, 29.5 / 22.8 / 26.2, 54.9 / 52.5 / 33.5).
 // ---------------------------------------------------------------------------
 constexpr int FG = 8;   // lanes per column
 

@@ -70,7 +70,7 @@ struct TileArgs {
     // already holds U^0
     void *eta_u, *eta_w;
     void *U_u, *U_w;
-    const void *R, *f, *H0, *W, *Av;
+    const void *R, *f, *H0, *W;
     const double *Av64;
     void *sum;                  // double2 running sum per triangle (both precisions)
     void *U0c;                  // U^0 (written by the first chunk unless direct)

@@ -362,8 +362,9 @@ template <> __device__ __forceinline__ float sesm_am<float>(const StepC &c, floa
     return __builtin_fmaf(c.am3_f, e2, __builtin_fmaf(c.am2_f, e1, __builtin_fmaf(c.am1_f, e, c.am0_f * en)));
 }
 
-// Sub-cell fluxes F . S_k of a transport F (FP64: as in tri_update).
-// FP32 form with mAe = -A_e (as in tri_update_f32)
+// Sub-cell fluxes F . S_k of a transport F, FP32, with mAe = -A_e: those of b and c, a's minus
+// their sum, as in tri_update (FP64: slot_fluxes, the three formed separately in the order of
+// the CPU definition).
 __device__ __forceinline__ void slot_fluxes_f32(float Fx, float Fy, float gbx, float gby, float gcx,
                                                 float gcy, float mAe, float &pa, float &pb,
                                                 float &pc) {
@@ -645,8 +646,8 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
     // the start of a launch, at the price of reading the padding and the owned ids; other
     // launches wait for the counts and read the entries in use alone.  The aligned rows
     // alone: 2.2M vertices FP32 2.42 -> 2.30 ms per call, FP64 4.19 -> 4.16, an ensemble of
-    // 24 basins 651 -> 616 us; issued early: 2,048 vertices FP64 92.3 -> 88.7 us, 11,397 FP32
-    // 108.3 -> 105.0.  (FP64 at six triangles per thread and 256 threads lost 3%.)
+    // 24 basins 651 -> 616 us; issued early (60 substeps): 2,048 vertices FP64 96.7 -> 92.1 us,
+    // FP32 92.5 -> 90.5.
     const int64_t le0 = static_cast<int64_t>(b) * a.se, lv0 = static_cast<int64_t>(b) * a.sv;
     const TileHdrK h = a.hdr[b];
     __builtin_amdgcn_sched_barrier(0);
@@ -770,7 +771,6 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
     // wait, then (B) the gathers through those indices, one wait before the barrier.
     // FP32 vertex gathers go straight to LDS (global_load_lds, the LDS address from
     // M0), FP64 ones through registers.
-    constexpr bool dma = F32;
     // inputs: SE ping-pongs (caller's arrays, workspace); SM: set 0 of the launch (the
     // caller's arrays at the first chunk, else what the previous chunk wrote)
     const bool pend = SM && ch > 0;   // SM: transport update of the previous substep pending
@@ -888,12 +888,10 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
     };
     // round B
     if constexpr (F32) {
-        if (dma) {
 #pragma unroll
-            for (int u = 0; u < VS; ++u) {
-                const int i = tid + u * BLOCK;
-                if (i < nv_load) dma_vertex(i, gv[u]);
-            }
+        for (int u = 0; u < VS; ++u) {
+            const int i = tid + u * BLOCK;
+            if (i < nv_load) dma_vertex(i, gv[u]);
         }
     }
     // FP64: the staged slots' gathers into registers, all in flight at once
@@ -971,13 +969,8 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int b, int G) {
     }
     // remainders: vertices beyond the staged slots, rows beyond the first chunk
     for (int i = tid + VS * BLOCK; i < nv_load; i += BLOCK) {
-        if constexpr (F32) {
-            if (dma) {
-                dma_vertex(i, lv[i]);
-                continue;
-            }
-        }
-        stage_vertex(i, lv[i]);
+        if constexpr (F32) dma_vertex(i, lv[i]);
+        else stage_vertex(i, lv[i]);
     }
     for (int i = tid + BLOCK; i < nrow4; i += BLOCK) reinterpret_cast<uint2 *>(sRow)[i] = ldp<nt>(crow + i);
     if constexpr (VI) {
@@ -1600,7 +1593,7 @@ __global__ void __launch_bounds__(256) k_adj_final(AdjArgs a, T *g_eta0, T *g_U0
 // arithmetic of adj_tri_at / adj_vtx_at operation for operation, so the gradients equal
 // those of the per-substep kernels bit for bit.  Inner step j runs the reverse of the
 // forward substep of trajectory slot s_hi - 1 - j; triangles E_lev and vertices
-// V_lev-1 are updated at level lev = cnt - j.  LDS holds the adjoint elevation, H0, A_v,
+// V_lev-1 are updated at level lev = cnt - j.  LDS holds the adjoint elevation, H0, 1/A_v,
 // the forward elevations of the launch's slots and the deposits (three slot terms and
 // lambda_H / 3 per triangle, at the forward kernel's flux positions); registers hold
 // the adjoint transport, the R gradient of owned triangles and the H0 gradient of owned

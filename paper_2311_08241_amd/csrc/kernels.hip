@@ -45,9 +45,10 @@ template <> __device__ __forceinline__ float copt<float>(const StepC &c) { retur
 // (mean H0 with linear_h).  FP64 adds the sum of the elevations, formed in the same order,
 // before the division by three: a triangle whose elevations cancel its depths has H = 0
 // exactly and is reported dry, where a mean depth plus a third of the elevations leaves a
-// rounding (6e-16 m at 10 m).  One multiplication more than a fused one, in the registers
-// of one number; the three depths apart would take 130 VGPRs at three triangles per thread
-// instead of 126, one 512-thread tile per CU instead of two.
+// rounding (6e-16 m at 10 m).  One multiplication more than a fused one (2,048 vertices FP64,
+// 30 substeps: 46.5 -> 46.7 us, 61,897 and 2.2M the same), in the registers of one number; the
+// three depths apart would take 130 VGPRs at three triangles per thread instead of 126, one
+// 512-thread tile per CU instead of two.
 template <typename T> struct TriDepth {
     T h;
 };
